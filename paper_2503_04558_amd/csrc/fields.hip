@@ -2,17 +2,11 @@
 // the integral form of the 3+1 Maxwell equations on the staggered Yee grid,
 // advanced by a predictor and ncorr semi-implicit corrector passes.
 //
-// One evaluation of the circulations is one stencil kernel (HBM-bound, no
-// matrix work), field_eval_kernel: a workgroup takes a tile of kTileR x
-// kTileC grid points, forms the auxiliary fields E_i, H_i of eqs. auxE /
-// auxH over the tile and a one-point halo in LDS -- metric coefficients
-// first (evaluated on the fly from tabulated r and sin, cos theta), then
-// averaged to the auxiliary field's location -- and then takes their
-// circulations (eqs. D-update, B-update; the axis rows of D^r by eq.
-// Dr-axis) and writes the predictor or corrector value of its points.
-// Guard rows are refilled (zero gradient) and the axis values of D^ph, B^th
-// set to zero by every pass; a damping layer scales the outer rows on the
-// last pass, and the columns beyond the axes are refreshed after the step.
+// A pass evaluates the auxiliary fields E_i, H_i of eqs. auxE / auxH, their
+// circulations (eqs. D-update, B-update; the axis rows of D^r by eq. Dr-axis)
+// and the predictor or corrector value of every point; the metric
+// coefficients are evaluated on the fly from tabulated r and sin, cos theta.
+// Up to four passes run in one launch (field_march_kernel).
 //
 // Locations, array element (i, j) of each component (r_x = exp(lnr0 + x
 // dlnr), theta_y = y dth): D^r, B^th, E_r, H_th at (i+1/2, j); D^th, B^r,
@@ -27,9 +21,6 @@
 namespace grpic {
 namespace {
 
-constexpr int kTileR = 8, kTileC = 64;                  // grid points per workgroup (2 per thread)
-constexpr int kAuxR = kTileR + 2, kAuxC = kTileC + 2;   // with a one-point halo
-
 __device__ __forceinline__ double rad(const FieldArgs& F, double x) { return exp(F.lnr0 + x * F.dlnr); }
 
 // sqrt(det gamma) of the Kerr-Schild 3-metric (App. A, M reinstated).
@@ -42,35 +33,6 @@ __device__ __forceinline__ double sqrt_gamma(double a, double M, double r, doubl
 struct Coef {
     double aGrr, aGrp, aGtt, aGpp, sgB;                 // alpha gamma_ij, sqrt(gamma) beta^r
 };
-
-// Coefficients at radius r and polar angle with sine s, cosine c, with
-// alpha = 1/sqrt(1 + z), z = 2 M r / rho^2: alpha gamma_rr = sqrt(1 + z),
-// alpha gamma_rph = -a sin^2 sqrt(1 + z), alpha gamma_thth = rho^2 alpha,
-// alpha gamma_phph = alpha Sigma sin^2 / rho^2, sqrt(gamma) beta^r =
-// rho^2 |sin| sqrt(1 + z) z / (1 + z) = 2 M r |sin| alpha.  One reciprocal
-// and one reciprocal square root per point.
-__device__ __forceinline__ Coef coef_at(double a, double M, double r, double s, double c) {
-    const double s2 = s * s, a2 = a * a, r2 = r * r;
-    const double rho2 = r2 + a2 * (c * c);
-    const double irho2 = rcp(rho2);
-    const double tMr = 2.0 * M * r;
-    double sq, alpha;
-    sqrt_rsqrt(1.0 + tMr * irho2, sq, alpha);
-    const double ra2 = r2 + a2;
-    const double Sigma = ra2 * ra2 - a2 * (ra2 - tMr) * s2;
-    Coef k;
-    k.aGrr = sq;
-    k.aGrp = -a * s2 * sq;
-    k.aGtt = alpha * rho2;
-    k.aGpp = alpha * Sigma * s2 * irho2;
-    k.sgB = tMr * fabs(s) * alpha;
-    return k;
-}
-
-// At grid position (x, y) = (hx / 2, hy / 2), hx >= -4 (x = -2), hy >= 0.
-__device__ __forceinline__ Coef coef_grid(const FieldArgs& F, int hx, int hy) {
-    return coef_at(F.a, F.M, F.rad[hx + 4], F.sn[hy], F.sn[field_nang(F.nth) + hy]);
-}
 
 struct Quad {
     double x[10], w[10];
@@ -136,190 +98,322 @@ __global__ __launch_bounds__(256) void field_tables_kernel(FieldArgs F, Quad Q) 
     }
 }
 
-// Axis values of D^ph and B^th set to zero (every row), then (second
-// launch) zero-gradient guard rows of the six components, all pitch
-// columns: rows -guard .. -1 copy row 0, rows above the last physical one
-// (nr for D^th, D^ph, B^r; nr - 1 for the components at i + 1/2) copy it.
-__global__ __launch_bounds__(256) void field_axis_kernel(FieldArgs F, FieldPtrs X) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int rows = F.nr + 1 + 2 * F.guard;
-    if (t >= (int64_t)rows * 2) return;
-    const int i = (int)(t >> 1) - F.guard, j = (t & 1) ? F.nth : 0;
-    X.c[2][F.at(i, j)] = 0.0;
-    X.c[4][F.at(i, j)] = 0.0;
-}
-
-__global__ __launch_bounds__(256) void field_guard_rows_kernel(FieldArgs F, FieldPtrs X) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int nrows = 2 * F.guard + 1;                  // -guard .. -1, nr .. nr + guard
-    if (t >= (int64_t)nrows * F.pitch) return;
-    const int r = (int)(t / F.pitch), jj = (int)(t % F.pitch) - F.guard;
-    const int i = r < F.guard ? r - F.guard : F.nr + (r - F.guard);
-    for (int c = 0; c < 6; ++c) {
-        const bool half = c == 0 || c == 4 || c == 5;
-        const int last = half ? F.nr - 1 : F.nr;
-        if (i >= 0 && i <= last) continue;              // row nr of D^th, D^ph, B^r is physical
-        const int src = i < 0 ? 0 : last;
-        X.c[c][F.at(i, jj)] = X.c[c][F.at(src, jj)];
-    }
-}
-
-// Columns beyond the axes, which the particles' CIC gather reads within
-// half a cell of an axis.  By axisymmetry (the extended chart's point
-// (r, -theta, phi) is (r, theta, phi + pi), where only the theta basis
-// vector is reversed) a component there is its value at the mirrored
-// location, negated for D^th and B^th.  Mirror pairs: integer columns
-// -m <-> m and nth + m <-> nth - m; columns at j + 1/2 (D^th, B^r, B^ph)
-// -m <-> m - 1 and nth - 1 + m <-> nth - m; every row, m = 1 .. guard.
-// Written columns and read columns are disjoint (nth > guard).
-__global__ __launch_bounds__(256) void field_axis_ghosts_kernel(FieldArgs F, FieldPtrs X) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int rows = F.nr + 1 + 2 * F.guard;
-    if (t >= (int64_t)rows * F.guard * 2) return;
-    const bool far = (t & 1) != 0;
-    const int m = (int)((t >> 1) % F.guard) + 1;
-    const int i = (int)((t >> 1) / F.guard) - F.guard;
-    for (int c = 0; c < 6; ++c) {
-        const double p = (c == 1 || c == 4) ? -1.0 : 1.0;
-        const bool half = c == 1 || c == 3 || c == 5;
-        const int dst = far ? (half ? F.nth - 1 + m : F.nth + m) : -m;
-        const int src = far ? F.nth - m : (half ? m - 1 : m);
-        X.c[c][F.at(i, dst)] = p * X.c[c][F.at(i, src)];
-    }
-}
-
-// The six auxiliary fields at grid point (i, j), -1 <= i <= nr, 0 <= j <=
-// nth, from the state X (guard rows filled): o[0..2] = E_r, E_th, E_ph,
-// o[3..5] = H_r, H_th, H_ph (E_th, H_r, H_ph only for j < nth, else 0).
-__device__ __forceinline__ void aux_at(const FieldArgs& F, const FieldPtrs& X, int i, int j, double o[6]) {
-    const uint32_t e = F.at(i, j), em = F.at(i - 1, j), ep = F.at(i + 1, j);
-    const double *Dr = X.c[0], *Dt = X.c[1], *Dp = X.c[2], *Br = X.c[3], *Bt = X.c[4], *Bp = X.c[5];
-    const int hx = 2 * i, hy = 2 * j;
-    // coefficients at (i +- 1/2, j), (i, j), (i + 1, j)
-    const Coef cRh = coef_grid(F, hx + 1, hy), cRm = coef_grid(F, hx - 1, hy);
-    const Coef cP = coef_grid(F, hx, hy), cPp = coef_grid(F, hx + 2, hy);
-    o[0] = cRh.aGrr * Dr[e] + 0.5 * (cP.aGrp * Dp[e] + cPp.aGrp * Dp[ep]);
-    o[2] = cP.aGpp * Dp[e] + 0.5 * (cRh.aGrp * Dr[e] + cRm.aGrp * Dr[em]) +
-           0.5 * (cRh.sgB * Bt[e] + cRm.sgB * Bt[em]);
-    o[4] = cRh.aGtt * Bt[e] + 0.5 * (cP.sgB * Dp[e] + cPp.sgB * Dp[ep]);
-    if (j < F.nth) {
-        // coefficients at (i, j + 1/2), (i + 1, j + 1/2), (i +- 1/2, j + 1/2)
-        const Coef cT = coef_grid(F, hx, hy + 1), cTp = coef_grid(F, hx + 2, hy + 1);
-        const Coef cBh = coef_grid(F, hx + 1, hy + 1), cBm = coef_grid(F, hx - 1, hy + 1);
-        o[1] = cT.aGtt * Dt[e] - 0.5 * (cBh.sgB * Bp[e] + cBm.sgB * Bp[em]);
-        o[3] = cT.aGrr * Br[e] + 0.5 * (cBh.aGrp * Bp[e] + cBm.aGrp * Bp[em]);
-        o[5] = cBh.aGpp * Bp[e] + 0.5 * (cT.aGrp * Br[e] + cTp.aGrp * Br[ep]) -
-               0.5 * (cT.sgB * Dt[e] + cTp.sgB * Dt[ep]);
-    } else {
-        o[1] = o[3] = o[5] = 0.0;
-    }
-}
-
-// One evaluation: the auxiliary fields of X over the tile and its halo in
-// LDS, then for each point of the tile the circulations C and the pass's
-// value of all six components.  The terms of a corrector that do not change
-// between passes are formed once: FIRST (the predictor, X = x0) writes
-// R = x0 + dt (w0 C - J) and the value x0 + dt (C - J); a corrector's value
-// is R + dt w1 C.  Elements a component does not update take x0 (R holds
-// it for the correctors; zero on the axes for D^ph, B^th); with L > 0 the
-// values at radial position x >= nr - L are scaled by 1 - d ((x - nr + L) /
-// L)^2 (the damping layer, on the step's last pass).  The zero-gradient
-// guard rows of out are written from the rows they copy.  out must not
-// alias X (other workgroups read X in their halo).
+// ---------------------------------------------------------------- the passes
+// A circulation pass reaches one row and one column to each side, so K passes
+// need a halo of K.  K + 1 waves run K consecutive passes over a strip of 64
+// columns and a segment of rows, marching up the rows: one wave loads them into
+// LDS (the iterate, R and the areas) two rows ahead, wave w runs pass w, taking
+// each row from its predecessor through LDS two rows behind it, and the last
+// one writes it.  A lane is a column: neighbours in theta are lane shifts,
+// neighbours in r the marching wave's own registers.  So an iterate, R and the
+// areas go through memory once per K passes, and a point's coefficients are
+// formed once per pass (a tile with a halo formed each four times over).
 //
-// Tile order: workgroup w runs on XCD w mod 8 (the dispatcher's round
-// robin), so logical tile (w mod 8) per + w / 8 gives each XCD a contiguous
-// band of tile rows in row-major order; the halo rows a tile shares with its
-// neighbours are then read through the same L2.
-template <bool FIRST>
-__global__ __launch_bounds__(256) void field_eval_kernel(FieldArgs F, FieldPtrs X, FieldPtrs x0, FieldPtrs R,
-                                                         FieldPtrs out, int L, double d, unsigned ntiles,
-                                                         unsigned per_xcd) {
-    __shared__ double aux[6][kAuxR][kAuxC];
-    const unsigned tile = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= ntiles) return;                          // whole workgroup: before any barrier
-    const int tiles_c = (F.nth + kTileC) / kTileC;      // columns 0 .. nth
-    const int i0 = (int)(tile / tiles_c) * kTileR, j0 = (int)(tile % tiles_c) * kTileC;
-    for (int e = threadIdx.x; e < kAuxR * kAuxC; e += blockDim.x) {
-        const int li = e / kAuxC, lj = e - li * kAuxC;
-        const int i = i0 - 1 + li, j = j0 - 1 + lj;
-        double o[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        if (i >= -1 && i <= F.nr && j >= 0 && j <= F.nth) aux_at(F, X, i, j, o);
-        for (int c = 0; c < 6; ++c) aux[c][li][lj] = o[c];
+// Measured, predictor and 7 correctors on 2048 x 2048: 500 us in two launches
+// of four passes, 0.87 GB of HBM traffic each, where one launch per pass took
+// 1560 us (0.82 to 1.12 GB each, 8 launches and 3 for the edges).  What bounds
+// it now is the marching step's latency: the waves of a workgroup meet at a
+// barrier each row, FP64 issue fills 45 % of the time and HBM runs at 3.5
+// TB/s.  Three passes per launch: 870 us, two: 810 (without the second strip,
+// which gave 685 for four); R and the areas re-read by each pass instead of
+// kept in LDS: 1.58 GB per launch, 765 us.
+constexpr int kMaxStages = 4;
+constexpr int kRing = 8;                                // rows of R and the areas in LDS: 2 kMaxStages are in use
+
+// The value of the lane below / above (lane - 1, lane + 1); zero where there is none.
+__device__ __forceinline__ double lane_below(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, true);   // wave_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_above(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xF, 0xF, true);   // wave_shl:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+struct StageArgs {
+    int strips, seg_rows;                               // strips of 64 columns, rows of a segment
+    unsigned nwg, per_xcd;                              // strips x segments, and an XCD's share of them
+    int last;                                           // the step's last launch: out is the state
+    int store_R;                                        // a later launch needs R
+    int damp_cells;
+    double damp_max;
+};
+
+// The metric factors of one column: sin^2, a^2 cos^2, |sin|, and of one row.
+struct ColK {
+    double s2, ac2, s;
+};
+struct RowK {
+    double r2, ra2, tMr;
+};
+__device__ __forceinline__ RowK row_at(const FieldArgs& F, double r) {
+    return {r * r, fma(r, r, F.a * F.a), 2.0 * F.M * r};
+}
+
+// Coefficients at a row and column, with alpha = 1/sqrt(1 + z), z = 2 M r /
+// rho^2: alpha gamma_rr = sqrt(1 + z), alpha gamma_rph = -a sin^2 sqrt(1 + z),
+// alpha gamma_thth = rho^2 alpha, alpha gamma_phph = alpha Sigma sin^2 / rho^2
+// with Sigma / rho^2 = r^2 + a^2 + z a^2 sin^2, and sqrt(gamma) beta^r =
+// 2 M r |sin| alpha.  The hardware estimates of 1 / rho^2 and (1 + z)^(-1/2)
+// (2^-23) take one third-order step each: d + d^2, and e/2 + 3 e^2 / 8 of the
+// residual.  (From one estimate, of (rho^2 (rho^2 + 2 M r))^(-1/2), a step is
+// 5 % faster and its error against 64-bit sums 5 to 10 % larger than that of
+// two Newton steps; this one's is 0 to 15 % smaller.)
+__device__ __forceinline__ Coef coef_point(const FieldArgs& F, const RowK& R, const ColK& C) {
+    const double rho2 = R.r2 + C.ac2;
+    const double i0 = __builtin_amdgcn_rcp(rho2);
+    const double d = fma(-rho2, i0, 1.0);
+    const double irho2 = fma(i0, fma(d, d, d), i0);
+    const double opz = fma(R.tMr, irho2, 1.0);
+    const double y0 = __builtin_amdgcn_rsq(opz);
+    const double g = opz * y0;
+    const double e = fma(-g, y0, 1.0), t = e * fma(0.375, e, 0.5);
+    const double alpha = fma(y0, t, y0);
+    Coef k;
+    k.aGrr = fma(g, t, g);
+    k.aGrp = (-F.a * C.s2) * k.aGrr;
+    k.aGtt = alpha * rho2;
+    k.aGpp = fma(R.tMr * irho2, F.a * F.a * C.s2, R.ra2) * (C.s2 * alpha);
+    k.sgB = (R.tMr * C.s) * alpha;
+    return k;
+}
+
+// What a marching pass carries from row to row: the products of row m - 1
+// that the averages onto the next row take, the half-row auxiliary fields'
+// own terms, the whole-row auxiliary fields of row m - 1 and the half-row
+// ones of row m - 2.
+struct MarchState {
+    double p1, p2, q1, q2, b1, b2, t1, t2;
+    double oDr, oBt, oBp;
+    double Et, Ep, Hr, Hp, Ht;
+};
+
+// The step's last pass: row r of the new state, with the damping layer
+// (values at radial position x >= nr - L scaled by 1 - d ((x - nr + L) /
+// L)^2), the guard rows, and the columns beyond the axes, which the
+// particles' gather reads within half a cell of an axis.  By axisymmetry (the
+// extended chart's point (r, -theta, phi) is (r, theta, phi + pi), where only
+// the theta basis vector is reversed) a component there is its value at the
+// mirrored location, negated for D^th and B^th: integer columns -m <-> m and
+// nth + m <-> nth - m, columns at j + 1/2 (D^th, B^r, B^ph) -m <-> m - 1 and
+// nth - 1 + m <-> nth - m, m = 1 .. guard (nth > guard).
+// Rows between the edges, which are nearly all, take no loop: this wave's
+// rows are what the others wait for.
+__device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs& out, const StageArgs& S, int r, int j,
+                                            int lane, bool owned, bool first_strip, bool last_strip, double v[6]) {
+    const int L = S.damp_cells;
+    if (L > 0 && r >= F.nr - L - 1) {                   // damping at x = r, r + 1/2
+        const double x_in = (double)(F.nr - L);
+        auto damp = [&](double x) {
+            const double q = (x - x_in) / L;
+            return x < x_in ? 1.0 : 1.0 - S.damp_max * q * q;
+        };
+        const double f_i = damp((double)r), f_h = damp(r + 0.5);
+        for (int c = 0; c < 6; ++c) v[c] *= c == 0 || c > 3 ? f_h : f_i;
     }
-    __syncthreads();
-    const double* T = F.tab;
-    const size_t S = F.plane;
-    for (int k = threadIdx.x; k < kTileR * kTileC; k += blockDim.x) {
-        const int li = k / kTileC, lj = k - li * kTileC;
-        const int i = i0 + li, j = j0 + lj;
-        if (i > F.nr || j > F.nth) continue;
-        const int a = li + 1, b = lj + 1;                // this point in the aux tile
-        const uint32_t e = F.at(i, j);
-        const double dr = F.drow[kDrPrimal * F.nrow + (i - kTableRowLo)];
-        const double drd = F.drow[kDrDual * F.nrow + (i - kTableRowLo)];
-        double f_i = 1.0, f_h = 1.0;                     // damping at x = i, i + 1/2
-        if (L > 0) {
-            const double x_in = (double)(F.nr - L);
-            auto damp = [&](double x) {
-                const double s = (x - x_in) / L;
-                return x < x_in ? 1.0 : 1.0 - d * s * s;
-            };
-            f_i = damp((double)i);
-            f_h = damp(i + 0.5);
-        }
-        auto put = [&](int c, double v) {
-            const bool half = c == 0 || c == 4 || c == 5;
-            const int last = half ? F.nr - 1 : F.nr;
-            v *= half ? f_h : f_i;
-            out.c[c][e] = v;
-            if (i == 0)
-                for (int g = 1; g <= F.guard; ++g) out.c[c][F.at(-g, j)] = v;
-            if (i == last)
-                for (int r = last + 1; r <= F.nr + F.guard; ++r) out.c[c][F.at(r, j)] = v;
+    const int fm = F.nth - j;
+    // row q of component c, with its mirrored columns
+    auto put = [&](int c, int q) {
+        const bool chalf = c == 1 || c == 3 || c == 5;
+        if (owned && !(chalf && fm == 0)) *elem(out.c[c], F.at(q, j)) = v[c];   // (a mirrored column there)
+        if (!first_strip && !last_strip) return;
+        const double mir = (c == 1 || c == 4) ? -v[c] : v[c];
+        const int near = chalf ? -j - 1 : -j;
+        if (owned && near < 0 && near >= -F.guard) *elem(out.c[c], F.at(q, near)) = mir;
+        if (owned && fm >= 1 && fm <= F.guard) *elem(out.c[c], F.at(q, (chalf ? 2 * F.nth - 1 : 2 * F.nth) - j)) = mir;
+    };
+    if (r > 0 && r < F.nr - 1) {
+        for (int c = 0; c < 6; ++c) put(c, r);
+        return;
+    }
+    for (int c = 0; c < 6; ++c) {
+        const bool half = c == 0 || c > 3, chalf = c == 1 || c == 3 || c == 5;
+        const int top = half ? F.nr - 1 : F.nr;
+        if (r > top) continue;
+        const int lo = r == 0 ? -F.guard : r, hi = r == top ? F.nr + F.guard : r;
+        for (int q = lo; q <= hi; ++q) put(c, q);
+        // the guard rows' columns beyond the mirrored ones repeat the edge row's
+        if (last_strip && lo < hi)
+            for (int p = F.nth + F.guard + (chalf ? 0 : 1) + lane; p < F.pitch - F.guard; p += 64)
+                for (int q = lo; q <= hi; ++q)
+                    if (q != r) *elem(out.c[c], F.at(q, p)) = *elem(out.c[c], F.at(r, p));
+    }
+}
+
+// K passes over one strip and segment.  FIRST: the launch's first pass is the
+// predictor (in is the start state X^n, whose axis values of D^ph, B^th count
+// as zero); it forms R = x0 + dt (w0 C - J) and the value x0 + dt (C - J),
+// every other pass's value is R + dt w1 C.  Rows beyond the edges repeat the
+// edge rows (zero gradient): a pass keeps the last row it was given, and at
+// row 0 takes it for row -1 first.  The step's last launch writes the state.
+//
+// in must not alias out (neighbouring workgroups read their halo of it).
+// Workgroup w runs on XCD w mod 8 (the dispatcher's round robin), so logical
+// index (w mod 8) per + w / 8 gives each XCD neighbouring strips, whose halo
+// columns then come through the same L2.
+template <int K, bool FIRST, int H>
+__global__ __launch_bounds__(64 * H * (K + 1)) __attribute__((amdgpu_waves_per_eu(3))) void field_march_kernel(
+    FieldArgs F, FieldPtrs in, FieldPtrs R, FieldPtrs out, StageArgs S, const double* __restrict__ T,
+    const double* __restrict__ rad, const double* __restrict__ drow) {
+    __shared__ double xrs[H][K][2][6][64];   // rows handed to pass w
+    __shared__ double ras[H][kRing][12][64]; // R (the predictor's x0 before it), then the inverse areas
+    __shared__ double jrs[FIRST ? H : 1][2][3][64];   // the predictor's currents
+    const unsigned wg = (blockIdx.x & 7u) * S.per_xcd + (blockIdx.x >> 3);
+    if (wg >= S.nwg) return;                            // whole workgroup: before any barrier
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int h = wave / (K + 1), w = wave % (K + 1) - 1;
+    auto& xr = xrs[h];
+    auto& ra = ras[h];
+    auto& jr = jrs[FIRST ? h : 0];
+    const int pairs = (S.strips + H - 1) / H;
+    const int strip = (int)(wg % (unsigned)pairs) * H + h;   // may be one past the last: an idle half
+    const int a = (int)(wg / (unsigned)pairs) * S.seg_rows, b = min(a + S.seg_rows, F.nr + 1);
+    const int j = strip * (64 - 2 * K) + lane, jc = min(j, F.nth);
+    const bool axis = j == 0 || j >= F.nth;
+    const int m0 = max(a - K, 0);                       // the first row read
+    const int steps = b - m0 + 2 * K;                   // row b comes to the last pass in the last one
+
+    if (w < 0) {                                        // the loading wave, two rows ahead
+        const size_t P = F.plane;
+        double q[2][21];
+        auto load = [&](int t, double o[21]) {          // what step t hands on: row m0 + t, and R, areas, currents of the one before
+            const int m = m0 + t;
+            const uint32_t ei = F.at(min(m, F.nr), jc), eh = F.at(min(m, F.nr - 1), jc);
+            const uint32_t e = F.at(min(max(m - 1, 0), F.nr), jc);
+            for (int c = 0; c < 6; ++c) o[c] = *elem(in.c[c], c == 0 || c > 3 ? eh : ei);
+            for (int c = 0; c < 6; ++c) o[6 + c] = *elem(FIRST ? in.c[c] : R.c[c], e);
+            for (int c = 0; c < 6; ++c) o[12 + c] = *elem(T + c * P, e);
+            if (FIRST)
+                for (int c = 0; c < 3; ++c) o[18 + c] = F.J[c] ? *elem(F.J[c], e) : 0.0;
         };
-        auto next = [&](int c, double C, double J) {
-            if (FIRST) {
-                const double x = x0.c[c][e];
-                R.c[c][e] = x + F.dt * (F.w0 * C - J);
-                return x + F.dt * (C - J);
+        auto hand = [&](int t, const double o[21]) {
+            const int m = m0 + t;
+            for (int c = 0; c < 6; ++c) {
+                const bool zero = FIRST && axis && (c == 2 || c == 4);
+                xr[0][m & 1][c][lane] = zero ? 0.0 : o[c];
+                ra[(m - 1) & (kRing - 1)][c][lane] = zero ? 0.0 : o[6 + c];
+                ra[(m - 1) & (kRing - 1)][6 + c][lane] = o[12 + c];
             }
-            return R.c[c][e] + F.dt * F.w1 * C;
+            if (FIRST)
+                for (int c = 0; c < 3; ++c) jr[(m - 1) & 1][c][lane] = o[18 + c];
         };
-        auto keep = [&](int c) {                         // an element the component does not update
-            if (FIRST) {
-                const double x = x0.c[c][e];
-                R.c[c][e] = x;
-                return x;
+        load(0, q[0]);
+        load(1, q[1]);
+        for (int t = 0; t < steps; t += 2) {
+            hand(t, q[0]);
+            load(t + 2, q[0]);
+            __syncthreads();
+            if (t + 1 < steps) {
+                hand(t + 1, q[1]);
+                load(t + 3, q[1]);
+                __syncthreads();
             }
-            return R.c[c][e];
-        };
-        auto cur = [&](int c, int t) { return FIRST && F.J[c] ? F.J[c][e] * T[t * S + e] : 0.0; };
-        const bool axis = j == 0 || j == F.nth;
-        if (i < F.nr) {                                  // D^r at (i+1/2, j), axes included
-            const double hp = j < F.nth ? aux[5][a][b] : 0.0, hm = j > 0 ? aux[5][a][b - 1] : 0.0;
-            put(0, next(0, (hp - hm) * T[kT_iADr * S + e], cur(0, kT_iADr)));
         }
-        // D^th at (i, j+1/2), B^r at (i, j+1/2)
-        put(1, j < F.nth ? next(1, (aux[5][a - 1][b] - aux[5][a][b]) * T[kT_iADt * S + e], cur(1, kT_iADt))
-                         : keep(1));
-        put(3, j < F.nth ? next(3, -(aux[2][a][b + 1] - aux[2][a][b]) * T[kT_iABr * S + e], 0.0) : keep(3));
-        // D^ph at (i, j), B^th at (i+1/2, j)
-        put(2, axis ? 0.0
-                    : next(2,
-                           ((aux[4][a][b] - aux[4][a - 1][b]) * F.dth + (aux[3][a][b - 1] - aux[3][a][b]) * drd) *
-                               T[kT_iADp * S + e],
-                           cur(2, kT_iADp)));
-        if (i < F.nr) {
-            put(4, axis ? 0.0 : next(4, -(aux[2][a][b] - aux[2][a + 1][b]) * T[kT_iABt * S + e], 0.0));
-            // B^ph at (i+1/2, j+1/2)
-            put(5, j < F.nth ? next(5,
-                                    -((aux[1][a + 1][b] - aux[1][a][b]) * F.dth +
-                                      (aux[0][a][b] - aux[0][a][b + 1]) * dr) *
-                                        T[kT_iABp * S + e],
-                                    0.0)
-                             : keep(5));
+        return;
+    }
+
+    const bool owned = j <= F.nth && (strip == 0 || lane >= K) && (strip == S.strips - 1 || lane < 64 - K);
+    const bool beyond = j >= F.nth;
+    ColK ci, ch;                                        // columns j and j + 1/2
+    {
+        const double* cs = F.sn + field_nang(F.nth);
+        const int hi = 2 * jc, hh = min(2 * jc + 1, 2 * F.nth);
+        const double si = F.sn[hi], cc = F.a * cs[hi], sh = F.sn[hh], chh = F.a * cs[hh];
+        ci = {si * si, cc * cc, fabs(si)};
+        ch = {sh * sh, chh * chh, fabs(sh)};
+    }
+    const int m_end = min(b + K - 1 - w, F.nr + 1);     // the last row this wave takes
+    double X[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    MarchState s = {};
+    for (int t = 0; t < steps; ++t) {
+        const int m = m0 + t - 2 * w - 1;
+        if (m >= m0 && m <= m_end) {
+            {
+                const double(*src)[64] = xr[w][m & 1];
+                if (m <= F.nr)
+                    for (int c = 1; c < 4; ++c) X[c] = src[c][lane];
+                if (m < F.nr) {
+                    X[0] = src[0][lane];
+                    X[4] = src[4][lane];
+                    X[5] = src[5][lane];
+                }
+            }
+            if (m == 0) {                               // row -1, a copy of row 0
+                const RowK ri = row_at(F, rad[2]), rh = row_at(F, rad[3]);
+                const Coef kR = coef_point(F, rh, ci), kP = coef_point(F, ri, ci);
+                const Coef kT = coef_point(F, ri, ch), kB = coef_point(F, rh, ch);
+                s = {kP.aGrp * X[2], kP.sgB * X[2], kR.aGrp * X[0], kR.sgB * X[4], kB.sgB * X[5], kB.aGrp * X[5],
+                     kT.aGrp * X[3], kT.sgB * X[1], kR.aGrr * X[0], kR.aGtt * X[4], kB.aGpp * X[5],
+                     0.0, 0.0, 0.0, 0.0, 0.0};
+            }
+            const RowK ri = row_at(F, rad[2 * m + 4]), rh = row_at(F, rad[2 * m + 5]);
+            const Coef kR = coef_point(F, rh, ci), kP = coef_point(F, ri, ci);
+            const Coef kT = coef_point(F, ri, ch), kB = coef_point(F, rh, ch);
+            const double np1 = kP.aGrp * X[2], np2 = kP.sgB * X[2];
+            const double nq1 = kR.aGrp * X[0], nq2 = kR.sgB * X[4];
+            const double nb1 = kB.sgB * X[5], nb2 = kB.aGrp * X[5];
+            const double nt1 = kT.aGrp * X[3], nt2 = kT.sgB * X[1];
+            // half-row auxiliary fields of row m - 1, whole-row ones of row m
+            const double Er = s.oDr + 0.5 * (s.p1 + np1);
+            const double Ht = s.oBt + 0.5 * (s.p2 + np2);
+            double Hp = s.oBp + 0.5 * (s.t1 + nt1) - 0.5 * (s.t2 + nt2);
+            const double Ep = kP.aGpp * X[2] + 0.5 * (nq1 + s.q1) + 0.5 * (nq2 + s.q2);
+            double Et = kT.aGtt * X[1] - 0.5 * (nb1 + s.b1);
+            double Hr = kT.aGrr * X[3] + 0.5 * (nb2 + s.b2);
+            if (beyond) Hp = Et = Hr = 0.0;             // no such location beyond the far axis
+            const int r = m - 1;                        // the row emitted
+            if (r >= m0) {
+                // circulations of row r
+                const double dr = drow[kDrPrimal * F.nrow + (r - kTableRowLo)];
+                const double drd = drow[kDrDual * F.nrow + (r - kTableRowLo)];
+                const double Hpm = lane_below(Hp), Hrm = lane_below(s.Hr);
+                const double Epp = lane_above(s.Ep), Erp = lane_above(Er);
+                double Cv[6];
+                Cv[0] = Hp - (j == 0 ? 0.0 : Hpm);
+                Cv[1] = s.Hp - Hp;
+                Cv[2] = (Ht - s.Ht) * F.dth + (Hrm - s.Hr) * drd;
+                Cv[3] = -(Epp - s.Ep);
+                Cv[4] = -(s.Ep - Ep);
+                Cv[5] = -((Et - s.Et) * F.dth + (Er - Erp) * dr);
+                double(*ring)[64] = ra[r & (kRing - 1)];
+                double v[6];
+                if (FIRST && w == 0) {
+                    double Rv[6];
+                    for (int c = 0; c < 6; ++c) {
+                        const double x0 = ring[c][lane], A = ring[6 + c][lane];
+                        const double C = Cv[c] * A, cur = c < 3 ? jr[r & 1][c][lane] * A : 0.0;
+                        Rv[c] = x0 + F.dt * (F.w0 * C - cur);
+                        v[c] = x0 + F.dt * (C - cur);
+                    }
+                    if (axis) Rv[2] = Rv[4] = 0.0;
+                    if (K > 1)
+                        for (int c = 0; c < 6; ++c) ring[c][lane] = Rv[c];
+                    if (S.store_R && owned && r >= a && r < b) {
+                        const uint32_t e = F.at(r, j);
+                        for (int c = 0; c < 6; ++c) *elem(R.c[c], e) = Rv[c];
+                    }
+                } else {
+                    for (int c = 0; c < 6; ++c) v[c] = ring[c][lane] + F.dt * F.w1 * (Cv[c] * ring[6 + c][lane]);
+                }
+                if (axis) v[2] = v[4] = 0.0;
+                if (w < K - 1) {
+                    for (int c = 0; c < 6; ++c) xr[w + 1][r & 1][c][lane] = v[c];
+                } else if (r >= a && r < b) {
+                    if (!S.last) {
+                        const uint32_t e = F.at(r, jc);
+                        if (owned)
+                            for (int c = 0; c < 6; ++c) *elem(out.c[c], e) = v[c];
+                    } else {
+                        store_state(F, out, S, r, j, lane, owned, strip == 0, strip == S.strips - 1, v);
+                    }
+                }
+            }
+            s = {np1, np2, nq1, nq2, nb1, nb2, nt1, nt2, kR.aGrr * X[0], kR.aGtt * X[4], kB.aGpp * X[5],
+                 Et, Ep, Hr, Hp, Ht};
         }
+        __syncthreads();
     }
 }
 
@@ -345,39 +439,72 @@ hipError_t launch_field_tables(const FieldArgs& F, const double* gx, const doubl
     return hipGetLastError();
 }
 
-// The step.  X's guard rows and axis values are set first; the predictor
-// reads X (iterate and start state) and writes W1 and the corrector's
-// constant part R; corrector passes alternate between W1 and W2 (a pass's
-// workgroups read their neighbours' halo of the previous iterate) and the
-// last writes X with the damping layer applied; then X's columns beyond the
-// axes are refreshed.  With no corrector the predictor writes X from a copy
-// of it in W2.
+// Workgroups of one launch.  A workgroup's LDS (73.7 to 76.8 KB per strip with
+// four passes) and its odd number of waves let a CU hold one workgroup of two
+// strips, or one of one strip (two five-wave workgroups do not share a CU:
+// their first SIMDs collide, measured 695 against 475 us per 2048 x 2048
+// step).  So: one strip per workgroup while segments of kMinSegRows rows fit
+// one round of 256 workgroups (a step of 256 x 256: 38 us against 46), else
+// two strips and segments cut for one round.
+constexpr int kCus = 256, kMinSegRows = 6;
+
+template <int K, bool FIRST>
+static void launch_march(const FieldArgs& F, FieldPtrs in, FieldPtrs R, FieldPtrs out, StageArgs S,
+                         hipStream_t stream) {
+    const int valid = 64 - 2 * K;
+    S.strips = 1 + (std::max(F.nth + 1 - 64, 0) + valid - 1) / valid;
+    const int most = (F.nr + kMinSegRows) / kMinSegRows;
+    const bool two = (int64_t)S.strips * most > kCus;
+    const int units = two ? (S.strips + 1) / 2 : S.strips;
+    const int segs = std::max(1, std::min(kCus / units, most));
+    S.seg_rows = (F.nr + segs) / segs;                  // ceil((nr + 1) / segs)
+    S.nwg = (unsigned)(units * ((F.nr + S.seg_rows) / S.seg_rows));
+    S.per_xcd = (S.nwg + 7) / 8;
+    const dim3 grid(8 * S.per_xcd);
+    if (two)
+        hipLaunchKernelGGL((field_march_kernel<K, FIRST, 2>), grid, dim3(128 * (K + 1)), 0, stream, F, in, R, out, S,
+                           F.tab, F.rad, F.drow);
+    else
+        hipLaunchKernelGGL((field_march_kernel<K, FIRST, 1>), grid, dim3(64 * (K + 1)), 0, stream, F, in, R, out, S,
+                           F.tab, F.rad, F.drow);
+}
+
+template <bool FIRST>
+static void launch_passes(int K, const FieldArgs& F, FieldPtrs in, FieldPtrs R, FieldPtrs out, const StageArgs& S,
+                          hipStream_t stream) {
+    if (K == 1) launch_march<1, FIRST>(F, in, R, out, S, stream);
+    else if (K == 2) launch_march<2, FIRST>(F, in, R, out, S, stream);
+    else if (K == 3) launch_march<3, FIRST>(F, in, R, out, S, stream);
+    else launch_march<4, FIRST>(F, in, R, out, S, stream);
+}
+
+// The step's 1 + ncorr passes in launches of up to kMaxStages, at least two:
+// the first reads X and leaves R, the last writes X, those between alternate
+// between W1 and W2.  A step of one pass (no corrector) reads a copy of X.
 hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, FieldPtrs W1, FieldPtrs W2, int ncorr,
                              int damp_cells, double damp_max, hipStream_t stream) {
-    const int64_t n_all = (int64_t)(F.nr + 1 + 2 * F.guard) * F.pitch;
-    const int64_t n_axis = (int64_t)(F.nr + 1 + 2 * F.guard) * 2, n_grow = (int64_t)(2 * F.guard + 1) * F.pitch;
-    const int64_t n_ghost = (int64_t)(F.nr + 1 + 2 * F.guard) * F.guard * 2;
-    const unsigned tiles = (unsigned)(((F.nr + kTileR) / kTileR) * ((F.nth + kTileC) / kTileC));
-    const unsigned per = (tiles + 7) / 8;
-    const dim3 grid(8 * per), block(256);
-    hipLaunchKernelGGL(field_axis_kernel, dim3(nb(n_axis)), block, 0, stream, F, X);
-    hipLaunchKernelGGL(field_guard_rows_kernel, dim3(nb(n_grow)), block, 0, stream, F, X);
+    StageArgs S{};
+    S.damp_cells = damp_cells;
+    S.damp_max = damp_max;
     if (ncorr == 0) {
-        hipLaunchKernelGGL(field_copy_kernel, dim3(nb(n_all)), block, 0, stream, W2, X, n_all);
-        hipLaunchKernelGGL(field_eval_kernel<true>, grid, block, 0, stream, F, W2, W2, R, X, damp_cells, damp_max,
-                           tiles, per);
-        hipLaunchKernelGGL(field_axis_ghosts_kernel, dim3(nb(n_ghost)), block, 0, stream, F, X);
+        const int64_t n_all = (int64_t)(F.nr + 1 + 2 * F.guard) * F.pitch;
+        hipLaunchKernelGGL(field_copy_kernel, dim3(nb(n_all)), dim3(256), 0, stream, W2, X, n_all);
+        S.last = 1;
+        launch_march<1, true>(F, W2, R, X, S, stream);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(field_eval_kernel<true>, grid, block, 0, stream, F, X, X, R, W1, 0, 0.0, tiles, per);
-    for (int it = 0; it < ncorr; ++it) {
-        const bool last = it == ncorr - 1;
-        const FieldPtrs cur = it % 2 == 0 ? W1 : W2;
-        const FieldPtrs nxt = last ? X : (it % 2 == 0 ? W2 : W1);
-        hipLaunchKernelGGL(field_eval_kernel<false>, grid, block, 0, stream, F, cur, X, R, nxt,
-                           last ? damp_cells : 0, damp_max, tiles, per);
+    const int passes = ncorr + 1;
+    const int launches = std::max(2, (passes + kMaxStages - 1) / kMaxStages);
+    FieldPtrs cur = X;
+    for (int g = 0; g < launches; ++g) {
+        const int K = passes / launches + (g < passes % launches ? 1 : 0);
+        S.last = g == launches - 1;
+        S.store_R = 1;
+        const FieldPtrs nxt = S.last ? X : (g % 2 == 0 ? W1 : W2);
+        if (g == 0) launch_passes<true>(K, F, cur, R, nxt, S, stream);
+        else launch_passes<false>(K, F, cur, R, nxt, S, stream);
+        cur = nxt;
     }
-    hipLaunchKernelGGL(field_axis_ghosts_kernel, dim3(nb(n_ghost)), block, 0, stream, F, X);
     return hipGetLastError();
 }
 
