@@ -166,11 +166,6 @@ int64_t sort_scan_blocks(int64_t len);
 void scan_exclusive(unsigned long long* a, int64_t len, unsigned long long* blocksums, hipStream_t stream);
 size_t sort_workspace_bytes(int nr, int nth);
 hipError_t launch_sort(const SortArgs& S, hipStream_t stream);
-// The anchor table of a tiling (r at the rows' corners, sin and cos at the
-// columns'), which depends on the grid only: written by the sort.
-hipError_t launch_anchor_table(double lnr0, double dlnr, double dth, int nr, int nth, double* anchors,
-                               hipStream_t stream);
-
 // The sort workspace that grpic_sort_noalloc uses: a static device array of
 // kSortScratchBytes per GPU; sort_scratch returns its address on the current
 // device (looked up on the first call there).

@@ -897,34 +897,6 @@ __global__ __launch_bounds__(THREADS) void push_deposit_split_tiled(const StepAr
     push_deposit_tiled_body<THREADS, true, SHORT, kBoris>(A, slices, slice_cap, slice_live, anchors);
 }
 
-// The anchor table of a tiling (layout in grpic_launch.hpp), from the same
-// anchor_r / anchor_sc as the untiled kernels' anchors.
-__global__ __launch_bounds__(256) void tile_anchor_table(const StepArgs A, double* __restrict__ anchors, int rows,
-                                                         int cols) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < rows) anchors[t] = anchor_r(A, t - kMarginRows);
-    if (t < cols) {
-        double s, c;
-        anchor_sc(A, t - kMarginCols, s, c);
-        anchors[rows + t] = s;
-        anchors[rows + cols + t] = c;
-    }
-}
-
-hipError_t launch_anchor_table(double lnr0, double dlnr, double dth, int nr, int nth, double* anchors,
-                               hipStream_t stream) {
-    StepArgs A{};
-    A.lnr0 = lnr0;
-    A.dlnr = dlnr;
-    A.dth = dth;
-    A.nr = nr;
-    A.nth = nth;
-    const int rows = anchor_table_rows(nr), cols = anchor_table_cols(nth);
-    hipLaunchKernelGGL(tile_anchor_table, dim3((unsigned)((std::max(rows, cols) + 255) / 256)), dim3(256), 0, stream,
-                       A, anchors, rows, cols);
-    return hipGetLastError();
-}
-
 // Q_ij += q w S_ij(x_p) over live particles (FP64 or split offsets).
 template <class T>
 __global__ __launch_bounds__(256) void charge_kernel(const StepArgs A, double* __restrict__ Q) {

@@ -1,8 +1,9 @@
 // sort.hip -- counting sort of particles by cell, and the tiling the tiled
 // push kernel runs on.
 //
-// histogram of live cells -> exclusive scan (two-level, 4096 entries per
-// block) -> [tiling: per-tile slice counts -> scan -> slice table] ->
+// histogram of live cells -> exclusive scan (4096 entries per block, two
+// launches) -> [tiling: per-tile slice counts of both cuts -> scan -> slice
+// tables] ->
 // scatter.  Histogram and scatter take a chunk of consecutive particles per
 // workgroup and count its cells in an LDS hash table first, so each distinct
 // cell of the chunk costs one global atomic: on the almost sorted input of a
@@ -12,6 +13,7 @@
 // order inside a cell is not specified.
 #include "grpic_launch.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace grpic {
@@ -28,48 +30,85 @@ size_t sort_workspace_bytes(int nr, int nth) {
     return (size_t)(len + sort_scan_blocks(len) + 1 + ntiles + 1) * sizeof(unsigned long long);
 }
 
-__global__ __launch_bounds__(256) void fill_u64(unsigned long long* __restrict__ a, int64_t n, unsigned long long v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) a[i] = v;
+// Before the histogram: the counts cleared and, with a tiling, its two slice
+// tables emptied and its anchor table written (from the same anchor_r /
+// anchor_sc as the untiled kernels' anchors).
+__global__ __launch_bounds__(256) void sort_setup(const SortArgs S, int64_t len, Slice* __restrict__ slices, int64_t cap,
+                                                  Slice* __restrict__ slices3, int64_t cap3,
+                                                  double* __restrict__ anchors, int rows, int cols) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < len) S.counts[t] = 0ull;
+    if (t < cap) slices[t] = Slice{-1, 0, 0};
+    if (t < cap3) slices3[t] = Slice{-1, 0, 0};
+    if (t >= rows && t >= cols) return;                 // without a tiling all four are zero
+    StepArgs A;
+    A.lnr0 = S.lnr0;
+    A.dlnr = S.dlnr;
+    A.dth = S.dth;
+    if (t < rows) anchors[t] = anchor_r(A, (int)t - kMarginRows);
+    if (t < cols) {
+        double s, c;
+        anchor_sc(A, (int)t - kMarginCols, s, c);
+        anchors[rows + t] = s;
+        anchors[rows + cols + t] = c;
+    }
 }
 
 // Chunk of consecutive particles per histogram / scatter workgroup, and the
 // LDS hash table that counts its cells: at most half full, so an empty slot
 // is always found.  A scatter workgroup waits once for its cells' atomics
-// (with return, at the memory side); 2048-particle chunks halve those waits
-// per particle and beat 1024 (7.6 against 8.3 ms per re-sort of 2e8, two
-// workgroups per CU instead of five) and 512 (9.2 ms).
+// (with return, at the memory side) and writes a run per distinct cell;
+// 2048-particle chunks halve both per particle and beat 1024 (scatter of a
+// drifted 2e8 6.4 against 8.1 ms; 2e7 particles at 5 per cell, drifted by
+// several rows, 1.20 against 1.34 ms).  Chunks dealt to the XCDs in bands
+// (neighbouring ones through one L2) write slower: 7.9 ms.  A slot's 8 bytes hold its cell and count and then, in the
+// scatter, the cell's reserved output index.
 constexpr int kChunkThreads = 256;
 constexpr int kChunkItems = 8;
 constexpr int kChunk = kChunkThreads * kChunkItems;
-constexpr int kHashSlots = 2 * kChunk;
-static_assert((kHashSlots & (kHashSlots - 1)) == 0, "power-of-two table");
+constexpr int kHashBits = 12;
+constexpr int kHashSlots = 1 << kHashBits;
+static_assert(kHashSlots == 2 * kChunk, "at most half full");
 constexpr int kEmpty = -1;
 
-struct CellTable {
-    int key[kHashSlots];               // cell, or kEmpty
-    int count[kHashSlots];             // particles of the chunk in that cell
+union CellSlot {
+    struct {
+        int key;                       // cell, or kEmpty
+        int count;                     // particles of the chunk in that cell
+    };
+    unsigned long long base;           // the scatter's output index of the first of them
 };
 
-__device__ __forceinline__ void table_clear(CellTable& T) {
-    for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads) {
-        T.key[e] = kEmpty;
-        T.count[e] = 0;
-    }
+__device__ __forceinline__ void table_clear(CellSlot* T) {
+    for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads) T[e].base = 0x00000000FFFFFFFFull;   // kEmpty, 0
+}
+
+// Slot of place t in probing order: blocks of 16 slots, all blocks' first
+// slots, then all their second ones, ...
+__device__ __forceinline__ int slot_of(int t) {
+    constexpr int kBlocks = kHashSlots / 16;
+    return (t & (kBlocks - 1)) << 4 | t / kBlocks;
 }
 
 // Slot of cell c (inserted if new); adds inc to its count and returns the
-// count before the add in old.  Multiplicative hashing spreads the cells of
-// neighbouring rows (c and c + nth) that a plain mask would collide.
-__device__ __forceinline__ int table_insert(CellTable& T, int c, int inc, int& old) {
-    int slot = (int)(((unsigned)c * 2654435761u) >> 21) & (kHashSlots - 1);
+// count before the add in old.  Blocks of 16 cells, whose counters share a
+// 128-byte line, are hashed (multiplicatively: cells c and c + nth of
+// neighbouring rows must not collide) and keep their cells' order inside the
+// block, so that consecutive threads of the flush add to consecutive
+// counters: an atomic per line instead of one per cell (histogram of 2e7
+// drifted particles on 2048 x 2048 0.58 -> 0.20 ms, re-sort of 2e8 0.80 ->
+// 0.54 ms).  Probing goes to the same place of the next block, and after the
+// last block to the next place, so it reaches every slot.
+__device__ __forceinline__ int table_insert(CellSlot* T, int c, int inc, int& old) {
+    int t = (c & 15) << (kHashBits - 4) | (int)(((unsigned)(c >> 4) * 2654435761u) >> (36 - kHashBits));
     for (int probe = 0; probe < kHashSlots; ++probe) {
-        const int k = atomicCAS(&T.key[slot], kEmpty, c);
+        const int slot = slot_of(t);
+        const int k = atomicCAS(&T[slot].key, kEmpty, c);
         if (k == kEmpty || k == c) {
-            old = atomicAdd(&T.count[slot], inc);
+            old = atomicAdd(&T[slot].count, inc);
             return slot;
         }
-        slot = (slot + 1) & (kHashSlots - 1);
+        t = (t + 1) & (kHashSlots - 1);
     }
     old = 0;                           // not reached: at most kChunk keys in 2 * kChunk slots
     return -1;
@@ -97,7 +136,7 @@ __device__ __forceinline__ void wave_runs(int c, bool valid, int& head, int& tai
 // Inserts the valid cells of one item per lane, one table access per run of
 // equal cells; returns the lane's slot (-1 if not valid) and its rank among
 // the chunk's particles of that cell.  Every lane of the wave must call it.
-__device__ __forceinline__ int wave_insert(CellTable& T, int c, bool valid, int& rank) {
+__device__ __forceinline__ int wave_insert(CellSlot* T, int c, bool valid, int& rank) {
     const int lane = threadIdx.x & 63;
     int head, tail;
     wave_runs(c, valid, head, tail);
@@ -116,7 +155,7 @@ __device__ __forceinline__ int64_t chunk_index(int k) {
 // Histogram of live cells: counts[c] += number of particles in cell c.
 __global__ __launch_bounds__(kChunkThreads) void sort_hist(const int32_t* __restrict__ cell, int64_t n, int ncell,
                                                            unsigned long long* __restrict__ counts) {
-    __shared__ CellTable T;
+    __shared__ CellSlot T[kHashSlots];
     int c[kChunkItems];
     for (int k = 0; k < kChunkItems; ++k) {
         const int64_t p = chunk_index(k);
@@ -130,7 +169,7 @@ __global__ __launch_bounds__(kChunkThreads) void sort_hist(const int32_t* __rest
     }
     __syncthreads();
     for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads)
-        if (T.key[e] != kEmpty) atomicAdd(counts + T.key[e], (unsigned long long)T.count[e]);
+        if (T[e].key != kEmpty) atomicAdd(counts + T[e].key, (unsigned long long)T[e].count);
 }
 
 // Inclusive scan of one value per thread across a 256-thread block.
@@ -146,8 +185,30 @@ __device__ __forceinline__ unsigned long long block_inclusive_scan(unsigned long
     return sh[threadIdx.x];
 }
 
-// In-place exclusive scan of each 4096-entry tile; the tile total goes to blocksums.
-__global__ __launch_bounds__(256) void scan_tiles(unsigned long long* __restrict__ a, int64_t len,
+// What scan_tiles sums at entry i: the array itself, or the slice counts of
+// tile i in both cuts, the cubic cut's in the upper 32 bits (their totals are
+// at most n / 192 + ntiles, far below 2^32).
+struct ScanSelf {
+    const unsigned long long* a;
+    __device__ unsigned long long operator()(int64_t i) const { return a[i]; }
+};
+struct ScanSlices {
+    const unsigned long long* offs;     // the scanned cell counts
+    int nth, tpr;
+    int64_t ntiles;
+    __device__ unsigned long long operator()(int64_t t) const {
+        if (t >= ntiles) return 0ull;
+        const int64_t i = t / tpr, jb = t - i * tpr;
+        const int64_t c0 = i * nth + jb * kTileCells;
+        const int64_t c1 = c0 + min((int64_t)kTileCells, nth - jb * kTileCells);
+        const unsigned long long cnt = offs[c1] - offs[c0];
+        return (cnt + kSliceThreads - 1) / kSliceThreads | ((cnt + kSliceThreads3 - 1) / kSliceThreads3) << 32;
+    }
+};
+
+// Exclusive scan of each 4096-entry tile of v into a; the tile total goes to blocksums.
+template <class V>
+__global__ __launch_bounds__(256) void scan_tiles(V values, unsigned long long* a, int64_t len,
                                                   unsigned long long* __restrict__ blocksums) {
     __shared__ unsigned long long sh[kScanThreads];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -155,7 +216,7 @@ __global__ __launch_bounds__(256) void scan_tiles(unsigned long long* __restrict
     unsigned long long tot = 0;
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = base + k;
-        v[k] = i < len ? a[i] : 0ull;
+        v[k] = i < len ? values(i) : 0ull;
         tot += v[k];
     }
     const unsigned long long incl = block_inclusive_scan(tot, sh);
@@ -168,69 +229,58 @@ __global__ __launch_bounds__(256) void scan_tiles(unsigned long long* __restrict
     if (threadIdx.x == kScanThreads - 1) blocksums[blockIdx.x] = incl;
 }
 
-// Exclusive scan of the tile totals by one block, in chunks of 256.
-__global__ __launch_bounds__(256) void scan_top(unsigned long long* __restrict__ bs, int64_t nb) {
-    __shared__ unsigned long long sh[kScanThreads];
-    unsigned long long carry = 0;
-    for (int64_t c0 = 0; c0 < nb; c0 += kScanThreads) {
-        const int64_t i = c0 + threadIdx.x;
-        const unsigned long long v = i < nb ? bs[i] : 0ull;
-        const unsigned long long incl = block_inclusive_scan(v, sh);
-        if (i < nb) bs[i] = carry + incl - v;
-        const unsigned long long total = sh[kScanThreads - 1];
-        __syncthreads();
-        carry += total;
+// Adds the totals of the tiles before it to each tile (every block sums them
+// itself: a launch fewer than a scan of the totals); copies of the result
+// go to offsets and its last entry to last, where given.
+__global__ __launch_bounds__(256) void scan_finish(unsigned long long* __restrict__ a, int64_t len,
+                                                   const unsigned long long* __restrict__ blocksums,
+                                                   int64_t* __restrict__ offsets, int64_t* __restrict__ last) {
+    __shared__ unsigned long long part[4];
+    unsigned long long v = 0;
+    for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) v += blocksums[i];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = part[0] + part[1] + part[2] + part[3];
+    for (int k = 0; k < kScanItems; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * kScanTile + k * 256 + threadIdx.x;
+        if (i >= len) return;
+        const unsigned long long x = a[i] + v;
+        a[i] = x;
+        if (offsets) offsets[i] = (int64_t)x;
+        if (last && i == len - 1) *last = (int64_t)x;
     }
-    if (threadIdx.x == 0) bs[nb] = carry;
-}
-
-__global__ __launch_bounds__(256) void scan_add(unsigned long long* __restrict__ a, int64_t len,
-                                                const unsigned long long* __restrict__ bs) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < len) a[i] += bs[i / kScanTile];
 }
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Exclusive scan of a[0..len) in place (a[len-1] should be a zero sentinel
-// so that it receives the total).
+// Exclusive scan of v[0..len) into a (v[len-1] should be a zero sentinel so
+// that a[len-1] receives the total).
+template <class V>
+static void scan_into(V v, unsigned long long* a, int64_t len, unsigned long long* blocksums, int64_t* offsets,
+                      int64_t* last, hipStream_t stream) {
+    const dim3 nb((unsigned)sort_scan_blocks(len));
+    hipLaunchKernelGGL(scan_tiles<V>, nb, dim3(kScanThreads), 0, stream, v, a, len, blocksums);
+    hipLaunchKernelGGL(scan_finish, nb, dim3(256), 0, stream, a, len, blocksums, offsets, last);
+}
+
 void scan_exclusive(unsigned long long* a, int64_t len, unsigned long long* blocksums, hipStream_t stream) {
-    const int64_t nb = sort_scan_blocks(len);
-    hipLaunchKernelGGL(scan_tiles, dim3((unsigned)nb), dim3(kScanThreads), 0, stream, a, len, blocksums);
-    hipLaunchKernelGGL(scan_top, dim3(1), dim3(kScanThreads), 0, stream, blocksums, nb);
-    hipLaunchKernelGGL(scan_add, dim3(nblk(len)), dim3(256), 0, stream, a, len, blocksums);
+    scan_into(ScanSelf{a}, a, len, blocksums, nullptr, nullptr, stream);
 }
 
-// Number of slices of each tile, from the scanned cell offsets.
-__global__ __launch_bounds__(256) void tile_slice_counts(const unsigned long long* __restrict__ offs, int nr, int nth,
-                                                         int tpr, int smax, unsigned long long* __restrict__ ns) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ntiles = (int64_t)nr * tpr;
-    if (t > ntiles) return;
-    if (t == ntiles) { ns[t] = 0ull; return; }
-    const int i = (int)(t / tpr), jb = (int)(t - (int64_t)i * tpr);
-    const int64_t c0 = (int64_t)i * nth + (int64_t)jb * kTileCells;
-    const int64_t c1 = c0 + min(kTileCells, nth - jb * kTileCells);
-    const unsigned long long cnt = offs[c1] - offs[c0];
-    ns[t] = (cnt + smax - 1) / smax;
-}
-
-__global__ __launch_bounds__(256) void slices_empty(Slice* __restrict__ out, int64_t cap) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < cap) out[i] = Slice{-1, 0, 0};
-}
-
-// Slice table: tile t's particles cut into ns balanced slices; slice L (in
+// Slice tables: tile t's particles cut into ns balanced slices; slice L (in
 // tile order) goes to entry (L % per_xcd) * 8 + L / per_xcd, the workgroup
-// that runs the L % per_xcd-th slice of XCD L / per_xcd's band.
+// that runs the L % per_xcd-th slice of XCD L / per_xcd's band.  Both cuts,
+// whose counts ScanSlices packed; the header.
 __global__ __launch_bounds__(256) void tile_slices(const unsigned long long* __restrict__ offs,
                                                    const unsigned long long* __restrict__ base, int nr, int nth,
-                                                   int tpr, int64_t n, int64_t cap, TilingHeader* hdr,
-                                                   Slice* __restrict__ out) {
+                                                   int tpr, int64_t n, TilingHeader* hdr, Slice* __restrict__ slices,
+                                                   int64_t cap, Slice* __restrict__ slices3, int64_t cap3) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t ntiles = (int64_t)nr * tpr;
-    if (t == 0 && hdr) {                                // the header: written with the CIC cut
-        hdr->nslices = (int64_t)base[ntiles];
+    const unsigned long long all = base[ntiles];
+    if (t == 0) {
+        hdr->nslices = (int64_t)(all & 0xFFFFFFFFull);
         hdr->n = n;
         hdr->n_sorted = (int64_t)offs[(int64_t)nr * nth];
         hdr->nr = nr;
@@ -244,44 +294,36 @@ __global__ __launch_bounds__(256) void tile_slices(const unsigned long long* __r
     const int64_t c1 = c0 + min(kTileCells, nth - jb * kTileCells);
     const int64_t start = (int64_t)offs[c0];
     const int64_t cnt = (int64_t)offs[c1] - start;
-    const int64_t b = (int64_t)base[t];
-    const int64_t ns = (int64_t)base[t + 1] - b;
-    if (ns <= 0) return;
-    const int64_t per_xcd = ((int64_t)base[ntiles] + 7) / 8;
-    const int64_t each = (cnt + ns - 1) / ns;
-    for (int64_t s = 0; s < ns; ++s) {
-        const int64_t s0 = s * each;
-        Slice sl;
-        sl.start = start + s0;
-        sl.len = (int32_t)(cnt - s0 < each ? cnt - s0 : each);
-        sl.tile = (int32_t)t;
-        const int64_t L = b + s;
-        const int64_t e = (L % per_xcd) * 8 + L / per_xcd;
-        if (e < cap) out[e] = sl;                        // always: cap >= nslices + 8
+    const unsigned long long b0 = base[t], b1 = base[t + 1];
+    for (int cut = 0; cut < 2; ++cut) {
+        const int64_t b = (int64_t)(b0 >> (32 * cut) & 0xFFFFFFFFull);
+        const int64_t ns = (int64_t)(b1 >> (32 * cut) & 0xFFFFFFFFull) - b;
+        if (ns <= 0) continue;
+        const int64_t per_xcd = ((int64_t)(all >> (32 * cut) & 0xFFFFFFFFull) + 7) / 8;
+        const int64_t each = (cnt + ns - 1) / ns;
+        Slice* out = cut == 0 ? slices : slices3;
+        const int64_t room = cut == 0 ? cap : cap3;
+        for (int64_t s = 0; s < ns; ++s) {
+            const int64_t s0 = s * each;
+            Slice sl;
+            sl.start = start + s0;
+            sl.len = (int32_t)(cnt - s0 < each ? cnt - s0 : each);
+            sl.tile = (int32_t)t;
+            const int64_t L = b + s;
+            const int64_t e = (L % per_xcd) * 8 + L / per_xcd;
+            if (e < room) out[e] = sl;                   // always: room >= nslices + 8
+        }
     }
-}
-
-__global__ __launch_bounds__(256) void sort_offsets_out(const unsigned long long* __restrict__ counts, int ncell,
-                                                        int64_t* __restrict__ offsets, int64_t* __restrict__ n_alive) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (offsets && i <= ncell) offsets[i] = (int64_t)counts[i];
-    if (i == ncell) *n_alive = (int64_t)counts[ncell];
-}
-
-// Elements of the output beyond the live count are marked removed.
-__global__ __launch_bounds__(256) void sort_mark_tail(int32_t* __restrict__ cell_out, int64_t n,
-                                                      const unsigned long long* __restrict__ total) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < n && p >= (int64_t)*total) cell_out[p] = -1;
 }
 
 // Scatter: counts[] holds each cell's next free output index; a chunk
 // reserves its particles' range of every cell with one atomic and places
-// them by their rank inside the chunk.
+// them by their rank inside the chunk.  Elements of the output beyond the
+// live count (counts[ncell], which no cell adds to) are marked removed by the
+// chunk of the same elements.
 template <class T>
 __global__ __launch_bounds__(kChunkThreads) void sort_scatter(const SortArgs S) {
-    __shared__ CellTable Tb;
-    __shared__ unsigned long long base[kHashSlots];
+    __shared__ CellSlot Tb[kHashSlots];
     int c[kChunkItems];
     for (int k = 0; k < kChunkItems; ++k) {
         const int64_t p = chunk_index(k);
@@ -299,17 +341,22 @@ __global__ __launch_bounds__(kChunkThreads) void sort_scatter(const SortArgs S) 
         ph[k] = valid && S.phi_in ? static_cast<const T*>(S.phi_in)[p] : T(0);
         tg[k] = valid && S.tag_in ? S.tag_in[p] : 0ull;
     }
+    const int64_t total = (int64_t)S.counts[S.ncell];
     table_clear(Tb);
     __syncthreads();
     int slot[kChunkItems], rank[kChunkItems];
     for (int k = 0; k < kChunkItems; ++k) slot[k] = wave_insert(Tb, c[k], c[k] >= 0 && c[k] < S.ncell, rank[k]);
     __syncthreads();
-    for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads)
-        if (Tb.key[e] != kEmpty) base[e] = atomicAdd(S.counts + Tb.key[e], (unsigned long long)Tb.count[e]);
+    for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads) {
+        const CellSlot sl = Tb[e];
+        if (sl.key != kEmpty) Tb[e].base = atomicAdd(S.counts + sl.key, (unsigned long long)sl.count);
+    }
     __syncthreads();
     for (int k = 0; k < kChunkItems; ++k) {
+        const int64_t p = chunk_index(k);
+        if (p >= total && p < S.n) S.cell_out[p] = -1;
         if (slot[k] < 0) continue;
-        const int64_t q = (int64_t)base[slot[k]] + rank[k];
+        const int64_t q = (int64_t)Tb[slot[k]].base + rank[k];
         S.cell_out[q] = c[k];
         for (int a = 0; a < 6; ++a) static_cast<T*>(S.out[a])[q] = v[k][a];
         S.sp_out[q] = spv[k];
@@ -322,36 +369,30 @@ static inline unsigned nchunk(int64_t n) { return (unsigned)((n + kChunk - 1) / 
 
 hipError_t launch_sort(const SortArgs& S, hipStream_t stream) {
     const int64_t len = (int64_t)S.ncell + 1;
-    hipLaunchKernelGGL(fill_u64, dim3(nblk(len)), dim3(256), 0, stream, S.counts, len, 0ull);
+    const int tpr = tiles_per_row(S.nth);
+    const int64_t ntiles = (int64_t)S.nr * tpr;
+    const TilingLayout L = S.tiling ? tiling_layout(S.n, S.nr, S.nth) : TilingLayout{};
+    Slice *slices = nullptr, *slices3 = nullptr;
+    double* anchors = nullptr;
+    if (S.tiling) {
+        slices = tiling_at<Slice>(S.tiling, L.slices);
+        slices3 = tiling_at<Slice>(S.tiling, L.slices3);
+        anchors = tiling_at<double>(S.tiling, L.anchors);
+    }
+    const int rows = S.tiling ? anchor_table_rows(S.nr) : 0, cols = S.tiling ? anchor_table_cols(S.nth) : 0;
+    const int64_t setup = std::max(std::max(len, std::max(L.cap, L.cap3)), (int64_t)std::max(rows, cols));
+    hipLaunchKernelGGL(sort_setup, dim3(nblk(setup)), dim3(256), 0, stream, S, len, slices, L.cap, slices3, L.cap3,
+                       anchors, rows, cols);
     if (S.n > 0)
         hipLaunchKernelGGL(sort_hist, dim3(nchunk(S.n)), dim3(kChunkThreads), 0, stream, S.cell_in, S.n, S.ncell, S.counts);
-    scan_exclusive(S.counts, len, S.blocksums, stream);
+    scan_into(ScanSelf{S.counts}, S.counts, len, S.blocksums, S.cell_offsets, S.n_alive, stream);
     if (S.tiling) {
-        const int tpr = tiles_per_row(S.nth);
-        const int64_t ntiles = (int64_t)S.nr * tpr;
-        const TilingLayout L = tiling_layout(S.n, S.nr, S.nth);
-        TilingHeader* hdr = static_cast<TilingHeader*>(S.tiling);
-        // the two cuts, one after the other (they share the tile_slices workspace)
-        for (int cut = 0; cut < 2; ++cut) {
-            const int smax = cut == 0 ? kSliceThreads : kSliceThreads3;
-            const int64_t cap = cut == 0 ? L.cap : L.cap3;
-            Slice* slices = tiling_at<Slice>(S.tiling, cut == 0 ? L.slices : L.slices3);
-            hipLaunchKernelGGL(tile_slice_counts, dim3(nblk(ntiles + 1)), dim3(256), 0, stream, S.counts, S.nr, S.nth,
-                               tpr, smax, S.tile_slices);
-            scan_exclusive(S.tile_slices, ntiles + 1, S.blocksums, stream);
-            hipLaunchKernelGGL(slices_empty, dim3(nblk(cap)), dim3(256), 0, stream, slices, cap);
-            hipLaunchKernelGGL(tile_slices, dim3(nblk(ntiles + 1)), dim3(256), 0, stream, S.counts, S.tile_slices,
-                               S.nr, S.nth, tpr, S.n, cap, cut == 0 ? hdr : nullptr, slices);
-        }
-        const hipError_t e = launch_anchor_table(S.lnr0, S.dlnr, S.dth, S.nr, S.nth,
-                                                 tiling_at<double>(S.tiling, L.anchors), stream);
-        if (e != hipSuccess) return e;
+        scan_into(ScanSlices{S.counts, S.nth, tpr, ntiles}, S.tile_slices, ntiles + 1, S.blocksums, nullptr, nullptr,
+                  stream);
+        hipLaunchKernelGGL(tile_slices, dim3(nblk(ntiles)), dim3(256), 0, stream, S.counts, S.tile_slices, S.nr, S.nth,
+                           tpr, S.n, static_cast<TilingHeader*>(S.tiling), slices, L.cap, slices3, L.cap3);
     }
-    hipLaunchKernelGGL(sort_offsets_out, dim3(nblk(len)), dim3(256), 0, stream, S.counts, S.ncell,
-                       S.cell_offsets, S.n_alive);
     if (S.n > 0) {
-        hipLaunchKernelGGL(sort_mark_tail, dim3(nblk(S.n)), dim3(256), 0, stream, S.cell_out, S.n,
-                           S.counts + S.ncell);
         if (S.elem == 8) hipLaunchKernelGGL(sort_scatter<double>, dim3(nchunk(S.n)), dim3(kChunkThreads), 0, stream, S);
         else hipLaunchKernelGGL(sort_scatter<float>, dim3(nchunk(S.n)), dim3(kChunkThreads), 0, stream, S);
     }
