@@ -26,6 +26,9 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed FP32 ops
     "-Wno-unused-command-line-argument",
 ]
+# The reverse sweep's loops use more 64-bit constants than registers are left:
+# formed where they are used, not ahead of the loops.
+SOURCE_FLAGS = {"adjoint.hip": ["-mllvm", "-disable-machine-licm", "-mllvm", "-amdgpu-use-amdgpu-trackers=1"]}
 
 
 def sources() -> list[str]:
@@ -34,7 +37,7 @@ def sources() -> list[str]:
 
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
-    cmd = [HIPCC, "-O3", *FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", src, "-o", obj]
+    cmd = [HIPCC, "-O3", *FLAGS, *SOURCE_FLAGS.get(os.path.basename(src), []), "-I", INCLUDE, "-I", CSRC, "-c", src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -488,7 +488,13 @@ static int backward_checked(const grpic_metric* metric, const grpic_grid* grid, 
     B.lnr0 = grid->lnr0; B.dlnr = grid->dlnr; B.dth = grid->dth;
     B.nr = grid->nr; B.nth = grid->nth; B.guard = grid->guard; B.pitch = grid->pitch;
     B.dt = dt; B.ncorr = ncorr; B.nsteps = nsteps; B.ckpt_every = ckpt_every; B.nsp = nsp;
-    for (int i = 0; i < nsp; ++i) { B.q[i] = species[i].q; B.m[i] = species[i].m; B.massless[i] = species[i].massless; }
+    B.idlnr = 1.0 / grid->dlnr; B.idth = 1.0 / grid->dth;
+    B.a2 = metric->a * metric->a; B.M2 = 2.0 * metric->M; B.M4a2 = 4.0 * metric->M * B.a2;
+    for (int i = 0; i < nsp; ++i) {
+        B.q[i] = species[i].q;
+        B.qm[i] = species[i].massless ? 0.0 : species[i].q / species[i].m;
+        B.massless[i] = species[i].massless;
+    }
     B.n = parts->n;
     B.first = first;
     B.count = count;

@@ -135,9 +135,10 @@ struct SortArgs {
 struct BackArgs {
     double a, M, lnr0, dlnr, dth;
     int nr, nth, guard, pitch;
+    double idlnr, idth, a2, M2, M4a2; // 1/dlnr, 1/dth, a^2, 2 M, 4 M a^2
     double dt;
     int ncorr, nsteps, ckpt_every, nsp;
-    double q[kMaxSpecies], m[kMaxSpecies];
+    double q[kMaxSpecies], qm[kMaxSpecies];   // charge, q/m (0 for massless species)
     int massless[kMaxSpecies];
     int64_t n;
     const double* w;
