@@ -136,6 +136,8 @@ void fill_common(grpic::StepArgs& A, const grpic_metric* m, const grpic_grid* g,
     memset(&A, 0, sizeof A);
     A.a = m ? m->a : 0.0;
     A.M = m ? m->M : 0.0;
+    A.a2 = A.a * A.a;
+    A.M2 = 2.0 * A.M;
     A.nr = g->nr; A.nth = g->nth; A.guard = g->guard; A.pitch = g->pitch;
     A.lnr0 = g->lnr0; A.dlnr = g->dlnr; A.dth = g->dth;
     A.idlnr = 1.0 / g->dlnr; A.idth = 1.0 / g->dth;

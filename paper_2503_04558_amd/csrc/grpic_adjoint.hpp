@@ -54,16 +54,6 @@ __host__ __device__ inline void stage_end() {
 #endif
 }
 
-// A polynomial's coefficient, on the GPU in scalar registers: loaded there
-// without vector instructions (the compiler otherwise moves each into vector
-// registers where it is used, a third of the series' instructions).
-__host__ __device__ inline double coeff(double c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+s"(c));
-#endif
-    return c;
-}
-
 constexpr int kMaxCorr = 8;            // predictor-corrector passes the adjoint supports
 
 // Grid and metric constants of a step.
@@ -86,37 +76,6 @@ struct Corner {
     Trig t;
     int ci, cj;
 };
-// sin and cos of a polar angle (a few multiples of pi at most): th less the
-// nearest k pi/2, pi/2 in two parts, then the Taylor series on [-pi/4, pi/4]
-// to x^17 and x^16 (the first omitted terms are below 1e-18).  The library's
-// pair takes four times the instructions and, for arguments that a polar
-// angle never has, the registers of a many-word reduction.
-__host__ __device__ inline void sincos_theta(double th, double& s, double& c) {
-    const double k = rint(th * 0.63661977236758134);
-    const double x1 = fma(-k, 1.5707963267948966, th);
-    const double x = fma(-k, 6.123233995736766e-17, x1), xl = fma(-k, 6.123233995736766e-17, x1 - x);
-    const double y = x * x;
-    double p = fma(coeff(1.0 / 355687428096000.0), y, coeff(-1.0 / 1307674368000.0));
-    p = fma(p, y, coeff(1.0 / 6227020800.0));
-    p = fma(p, y, coeff(-1.0 / 39916800.0));
-    p = fma(p, y, coeff(1.0 / 362880.0));
-    p = fma(p, y, coeff(-1.0 / 5040.0));
-    p = fma(p, y, coeff(1.0 / 120.0));
-    p = fma(p, y, coeff(-1.0 / 6.0));
-    const double sn = x + fma(p * y, x, xl);
-    double q = fma(coeff(1.0 / 20922789888000.0), y, coeff(-1.0 / 87178291200.0));
-    q = fma(q, y, coeff(1.0 / 479001600.0));
-    q = fma(q, y, coeff(-1.0 / 3628800.0));
-    q = fma(q, y, coeff(1.0 / 40320.0));
-    q = fma(q, y, coeff(-1.0 / 720.0));
-    q = fma(q, y, coeff(1.0 / 24.0));
-    q = fma(q, y, -0.5);
-    const double cs = 1.0 + fma(q, y, -x * xl);
-    const int n = (int)k;
-    const double ss = (n & 1) ? cs : sn, cc = (n & 1) ? sn : cs;
-    s = (n & 2) ? -ss : ss;
-    c = ((n + 1) & 2) ? -cc : cc;
-}
 __host__ __device__ inline Trig trig_plain(const Geo& G, double xi, double eta) {
     Trig t;
     t.r = ::exp(G.lnr0 + xi * G.dlnr);
@@ -135,32 +94,14 @@ template <bool SMALL>
 __host__ __device__ inline Trig trig_at(const Geo& G, const Corner& k, double xi, double eta) {
     if (!SMALL) return trig_plain(G, xi, eta);
     Trig t;
-    const double x = (xi - (double)k.ci) * G.dlnr;
-    double p = fma(coeff(1.0 / 3628800.0), x, coeff(1.0 / 362880.0));      // exp_small's series
-    p = fma(p, x, coeff(1.0 / 40320.0));
-    p = fma(p, x, coeff(1.0 / 5040.0));
-    p = fma(p, x, coeff(1.0 / 720.0));
-    p = fma(p, x, coeff(1.0 / 120.0));
-    p = fma(p, x, coeff(1.0 / 24.0));
-    p = fma(p, x, coeff(1.0 / 6.0));
-    p = fma(p, x, 0.5);
-    p = fma(p, x, 1.0);
-    t.r = k.t.r * fma(p, x, 1.0);
     if (k.t.s >= kPoleSin) {
-        const double y = (eta - (double)k.cj) * G.dth, y2 = y * y;         // sincos_small's
-        double ps = fma(coeff(1.0 / 362880.0), y2, coeff(-1.0 / 5040.0));
-        ps = fma(ps, y2, coeff(1.0 / 120.0));
-        ps = fma(ps, y2, coeff(-1.0 / 6.0));
-        const double sy = fma(ps * y2, y, y);
-        double pc = fma(coeff(-1.0 / 3628800.0), y2, coeff(1.0 / 40320.0));
-        pc = fma(pc, y2, coeff(-1.0 / 720.0));
-        pc = fma(pc, y2, coeff(1.0 / 24.0));
-        pc = fma(pc, y2, -0.5);
-        const double cy = fma(pc, y2, 1.0);
+        t.r = k.t.r * exp_small<false>((xi - (double)k.ci) * G.dlnr);
+        double sy, cy;
+        sincos_small<false>((eta - (double)k.cj) * G.dth, sy, cy);
         t.s = fma(k.t.s, cy, k.t.c * sy);
         t.c = fma(k.t.c, cy, -(k.t.s * sy));
     } else {
-        sincos_theta(eta * G.dth, t.s, t.c);
+        return trig_plain(G, xi, eta);
     }
     return t;
 }
@@ -187,13 +128,11 @@ __host__ __device__ inline RhsTerms rhs_terms(const Geo& G, double eps, const Tr
     m.sc = t.s * t.c;
     const double rho2 = r2 + a2 * (t.c * t.c), Q = rho2 + T;
     m.ra2 = r2 + a2;
-    const double rs2 = t.r * m.s2, rQ = rho2 * Q;
-    const double iP = inv_(rs2 * rQ);
-    const double x1 = rQ * iP, x2 = rs2 * iP;              // 1/(r sin^2), 1/(rho^2 Q)
-    m.ir = m.s2 * x1;
-    m.is2 = t.r * x1;
-    m.irho2 = Q * x2;
-    m.iQ = rho2 * x2;
+    // 1/sin^2 on its own: near an axis the result hangs on how it is rounded
+    m.ir = inv_(t.r);
+    m.is2 = inv_(m.s2);
+    m.irho2 = inv_(rho2);
+    m.iQ = inv_(Q);
     m.beta = T * m.iQ;
     m.iR = rho2 * m.iQ;
     m.R = Q * m.irho2;
@@ -270,8 +209,7 @@ enum { M_ALPHA, M_IALPHA, M_GRR, M_GRP, M_GTT, M_GPP, M_HRR, M_HRP, M_HTT, M_HPP
 __host__ __device__ inline void metric_at(const Geo& G, const Trig& t, double m[M_N]) {
     const double a = G.a, a2 = G.a2, r2 = t.r * t.r, s2 = t.s * t.s, T = G.M2 * t.r;
     const double rho2 = r2 + a2 * (t.c * t.c), Q = rho2 + T, ra2 = r2 + a2;
-    const double rQ = rho2 * Q, iP = inv_(s2 * rQ);
-    const double x2 = s2 * iP, irho2 = Q * x2, iQ = rho2 * x2, is2 = rQ * iP;
+    const double irho2 = inv_(rho2), iQ = inv_(Q), is2 = inv_(s2);
     const double z = T * irho2, R = 1.0 + z;
     sqrt_inv_(R, m[M_IALPHA], m[M_ALPHA]);
     m[M_GRR] = R;

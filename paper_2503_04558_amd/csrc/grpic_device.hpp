@@ -18,7 +18,7 @@ constexpr int kMaxSpecies = 8;
 
 // Everything a push+deposit launch needs, passed by value.
 struct StepArgs {
-    double a, M;
+    double a, M, a2, M2;                    // a2 = a^2, M2 = 2 M
     int nr, nth, guard, pitch;
     double lnr0, dlnr, dth;
     double idlnr, idth;                     // 1/dlnr, 1/dth
@@ -50,31 +50,28 @@ struct Metric {
     R ialpha;                               // 1/alpha = sqrt(1+z)
 };
 
-// 1/x from the hardware reciprocal estimate, refined by two Newton steps for
-// double (a few ulp, no division sequence); float takes the estimate (1 ulp).
+// 1/x from the hardware reciprocal estimate (2^-23) and one third-order step
+// on its residual e = 1 - x r: r (1 + e + e^2), about an ulp; float takes the
+// estimate (1 ulp).
 __device__ __forceinline__ double rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }   // 1 ulp
 
 // sqrt(x) and 1/sqrt(x) together, for x >= 1 (or a positive normal x):
-// double refines the hardware reciprocal-square-root estimate y by two
-// coupled Newton steps on g ~ sqrt(x) = x y and h ~ 1/(2 sqrt(x)) = y/2
-// (residual r = 1/2 - g h; each step squares the relative error, so a few
-// ulp remain); float takes the estimate (1 ulp) and one product.
+// double takes one third-order step from the hardware estimate y of 1/sqrt(x)
+// (2^-23), with the residual e = 1 - x y^2 the factor 1 + e/2 + 3 e^2/8 on y
+// and on x y (about an ulp each); float takes the estimate (1 ulp) and one
+// product.
 __device__ __forceinline__ void sqrt_rsqrt(double x, double& sq, double& rsq) {
     const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    r = fma(-g, h, 0.5);
-    sq = fma(g, r, g);
-    rsq = 2.0 * fma(h, r, h);
+    const double g = x * y;
+    const double e = fma(-g, y, 1.0);
+    const double t = e * fma(0.375, e, 0.5);
+    sq = fma(g, t, g);
+    rsq = fma(y, t, y);
 }
 __device__ __forceinline__ void sqrt_rsqrt(float x, float& sq, float& rsq) {
     rsq = __builtin_amdgcn_rsqf(x);
@@ -113,6 +110,51 @@ __device__ __forceinline__ void ks_metric(R a, R M, R r, R s, R c, Metric<R>& k)
     k.sqrtg = rho2 * s * sq;
 }
 
+// A polynomial's coefficient, on the GPU in scalar registers: loaded there
+// without vector instructions (the compiler otherwise moves each into vector
+// registers where it is used, a third of the series' instructions).
+__host__ __device__ inline double coeff(double c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(c));
+#endif
+    return c;
+}
+
+// sin and cos of a polar angle (a few multiples of pi at most): th less the
+// nearest k pi/2, pi/2 in two parts, then the Taylor series on [-pi/4, pi/4]
+// to x^17 and x^16 (the first omitted terms are below 1e-18).  The library's
+// pair takes four times the instructions and, for arguments that a polar
+// angle never has, the registers of a many-word reduction.
+__host__ __device__ inline void sincos_theta(double th, double& s, double& c) {
+    const double k = rint(th * 0.63661977236758134);
+    const double x1 = fma(-k, 1.5707963267948966, th);
+    const double x = fma(-k, 6.123233995736766e-17, x1), xl = fma(-k, 6.123233995736766e-17, x1 - x);
+    const double y = x * x;
+    double p = fma(coeff(1.0 / 355687428096000.0), y, coeff(-1.0 / 1307674368000.0));
+    p = fma(p, y, coeff(1.0 / 6227020800.0));
+    p = fma(p, y, coeff(-1.0 / 39916800.0));
+    p = fma(p, y, coeff(1.0 / 362880.0));
+    p = fma(p, y, coeff(-1.0 / 5040.0));
+    p = fma(p, y, coeff(1.0 / 120.0));
+    p = fma(p, y, coeff(-1.0 / 6.0));
+    const double sn = x + fma(p * y, x, xl);
+    double q = fma(coeff(1.0 / 20922789888000.0), y, coeff(-1.0 / 87178291200.0));
+    q = fma(q, y, coeff(1.0 / 479001600.0));
+    q = fma(q, y, coeff(-1.0 / 3628800.0));
+    q = fma(q, y, coeff(1.0 / 40320.0));
+    q = fma(q, y, coeff(-1.0 / 720.0));
+    q = fma(q, y, coeff(1.0 / 24.0));
+    q = fma(q, y, -0.5);
+    const double cs = 1.0 + fma(q, y, -x * xl);
+    const int n = (int)k;
+    const double ss = (n & 1) ? cs : sn, cc = (n & 1) ? sn : cs;
+    s = (n & 2) ? -ss : ss;
+    c = ((n + 1) & 2) ? -cc : cc;
+}
+__device__ __forceinline__ void sincos_theta(float th, float& s, float& c) {
+    s = sin(th);
+    c = cos(th);
+}
 // exp(x), sin(y), cos(y) for the small offsets of the predictor-corrector
 // points from a particle's start cell: Taylor polynomials, within an ulp or
 // two for |x|, |y| <= kSmallArg.  A point of a step is less than two cells
@@ -126,13 +168,16 @@ constexpr double kTinyArg = 0.005;
 // Within ~5.7 degrees of a pole (anchor sin(theta) < kPoleSin) sin and cos
 // are taken from theta = eta * dth directly: there the centrifugal terms
 // (gamma^phph ~ 1/sin^2) amplify how sin(theta) is rounded, and this keeps
-// the rounding the same as in the plain formula.
+// the rounding the same as in the plain formula (sincos_theta is within 0.51
+// ulp there).  With the library's sin and cos in place of sincos_theta the
+// tiled push holds 125 registers instead of 114 and its kernel has 40 % more
+// instructions.
 constexpr double kPoleSin = 0.1;
 
 // SHORT selects the short series (a launch-uniform choice made once per
 // particle step, so that each variant is straight-line code).
 template <bool SHORT, class R>
-__device__ __forceinline__ R exp_small(R x) {
+__host__ __device__ __forceinline__ R exp_small(R x) {
     if constexpr (std::is_same<R, float>::value) {
         // float: the series cut where the next term is below 1e-9 (|x| <= kSmallArg)
         float p = 1.0f / 120.0f;
@@ -142,17 +187,18 @@ __device__ __forceinline__ R exp_small(R x) {
         p = fmaf(p, x, 1.0f);
         return fmaf(p, x, 1.0f);
     } else {
-        R p = R(1.0 / 120.0);
+        R p;
         if constexpr (!SHORT) {
-            p = R(1.0 / 3628800.0);
-            p = fma(p, x, R(1.0 / 362880.0));
-            p = fma(p, x, R(1.0 / 40320.0));
-            p = fma(p, x, R(1.0 / 5040.0));
-            p = fma(p, x, R(1.0 / 720.0));
-            p = fma(p, x, R(1.0 / 120.0));
+            p = fma(coeff(1.0 / 3628800.0), x, coeff(1.0 / 362880.0));
+            p = fma(p, x, coeff(1.0 / 40320.0));
+            p = fma(p, x, coeff(1.0 / 5040.0));
+            p = fma(p, x, coeff(1.0 / 720.0));
+            p = fma(p, x, coeff(1.0 / 120.0));
+            p = fma(p, x, coeff(1.0 / 24.0));
+        } else {
+            p = fma(coeff(1.0 / 120.0), x, coeff(1.0 / 24.0));
         }
-        p = fma(p, x, R(1.0 / 24.0));
-        p = fma(p, x, R(1.0 / 6.0));
+        p = fma(p, x, coeff(1.0 / 6.0));
         p = fma(p, x, R(0.5));
         p = fma(p, x, R(1.0));
         return fma(p, x, R(1.0));
@@ -160,7 +206,7 @@ __device__ __forceinline__ R exp_small(R x) {
 }
 
 template <bool SHORT, class R>
-__device__ __forceinline__ void sincos_small(R y, R& sn, R& cs) {
+__host__ __device__ __forceinline__ void sincos_small(R y, R& sn, R& cs) {
     const R y2 = y * y;
     if constexpr (std::is_same<R, float>::value) {
         const float ps = fmaf(1.0f / 120.0f, y2, -1.0f / 6.0f);
@@ -168,17 +214,18 @@ __device__ __forceinline__ void sincos_small(R y, R& sn, R& cs) {
         const float pc = fmaf(1.0f / 24.0f, y2, -0.5f);
         cs = fmaf(pc, y2, 1.0f);
     } else {
-        R ps = R(1.0 / 120.0), pc = R(1.0 / 24.0);
+        R ps, pc;
         if constexpr (!SHORT) {
-            ps = R(1.0 / 362880.0);
-            ps = fma(ps, y2, R(-1.0 / 5040.0));
-            ps = fma(ps, y2, R(1.0 / 120.0));
-            pc = R(-1.0 / 3628800.0);
-            pc = fma(pc, y2, R(1.0 / 40320.0));
-            pc = fma(pc, y2, R(-1.0 / 720.0));
-            pc = fma(pc, y2, R(1.0 / 24.0));
+            ps = fma(coeff(1.0 / 362880.0), y2, coeff(-1.0 / 5040.0));
+            ps = fma(ps, y2, coeff(1.0 / 120.0));
+            ps = fma(ps, y2, coeff(-1.0 / 6.0));
+            pc = fma(coeff(-1.0 / 3628800.0), y2, coeff(1.0 / 40320.0));
+            pc = fma(pc, y2, coeff(-1.0 / 720.0));
+            pc = fma(pc, y2, coeff(1.0 / 24.0));
+        } else {
+            ps = fma(coeff(1.0 / 120.0), y2, coeff(-1.0 / 6.0));
+            pc = coeff(1.0 / 24.0);
         }
-        ps = fma(ps, y2, R(-1.0 / 6.0));
         sn = fma(ps * y2, y, y);
         pc = fma(pc, y2, R(-0.5));
         cs = fma(pc, y2, R(1.0));
@@ -232,15 +279,11 @@ __device__ __forceinline__ void point_at(const StepArgs& A, const Anchor<R>& an,
             s = fma(an.s, cy, an.c * sy);
             c = fma(an.c, cy, -(an.s * sy));
         } else {
-            const R th = eta * R(A.dth);
-            s = sin(th);
-            c = cos(th);
+            sincos_theta(eta * R(A.dth), s, c);
         }
     } else {
         r = exp(R(A.lnr0) + xi * R(A.dlnr));
-        const R th = eta * R(A.dth);
-        s = sin(th);
-        c = cos(th);
+        sincos_theta(eta * R(A.dth), s, c);
     }
 }
 
@@ -261,44 +304,71 @@ __device__ __forceinline__ void point_rel(const StepArgs& A, const Anchor<R>& an
     } else {
         r = exp(R(A.lnr0) + (R(an.ci) + dxi) * R(A.dlnr));
     }
-    const R th = (R(an.cj) + deta) * R(A.dth);
-    s = sin(th);
-    c = cos(th);
+    sincos_theta((R(an.cj) + deta) * R(A.dth), s, c);
 }
 
 // Geodesic right-hand side of eq. particle-eom (no Lorentz force) in grid
 // units at the point with radius r and polar angle of sine s, cosine c:
 // f = (dxi/dt, deta/dt, dphi/dt, du_r/dt, du_th/dt), du_ph/dt = 0.  App. A's
 // lapse, shift and gamma^ij and their r and theta derivatives are
-// substituted into it, so that it takes two hardware estimates:
-//  - with Q = rho^2 + 2Mr = rho^2 (1 + z), the reciprocals of r, sin^2,
-//    rho^2 and Q come from one reciprocal of r sin^2 rho^2 Q (double; float
-//    takes two, of r sin^2 and of rho^2 Q, to stay in range);
-//  - u^0 = sqrt(eps + u^2)/alpha = sqrt((eps + u^2) Q / rho^2) and 1/u^0 come
-//    from one square root;
-//  - alpha = (1+z)^(-1/2) and beta^r = z/(1+z) = 2Mr/Q give -alpha u^0
-//    d alpha = u^0 d beta^r / 2, with d beta^r = 2M (rho^2 - 2r^2)/Q^2 in r
-//    and 4 M a^2 r sin cos / Q^2 in theta;
-//  - the gamma^ij derivatives share their factor 1/rho^4, so the quadratic
-//    form u_i u_j d gamma^ij is summed inside it.
-template <class R>
-__device__ __forceinline__ void geodesic_rhs_point(const StepArgs& A, R eps, R r, R s, R c,
-                                                   R ur, R ut, R up, R f[5]) {
+// substituted into it, so that it takes two hardware estimates: with rho^2 =
+// r^2 + a^2 cos^2, T = 2 M r, Q = rho^2 + T = rho^2 (1 + z), beta^r = T / Q,
+//  - the reciprocals of r, sin^2, rho^2 and Q come from one reciprocal of
+//    r sin^2 rho^2 Q;
+//  - with y = u_ph / sin^2, W = a u_r + y, Z = a sin^2 u_r + u_ph and x =
+//    (u_th^2 + W u_ph + a u_r Z) / rho^2, u^2 = x + u_r^2 (1 - beta^r), and
+//    u^0 = sqrt((eps + u^2) Q / rho^2) and 1/u^0 come from one square root;
+//  - with g = 1 / (rho^2 u^0), v = u_r / u^0 and P = (r^2 + a^2) u_r + a u_ph
+//    the velocities are g P - beta^r (1 + v), g u_th, g W;
+//  - alpha^2 = 1 - beta^r turns the lapse derivative into the shift's: the
+//    forces are d beta^r (u^0 + u_r)(1 + v) / 2 with d beta^r = 2 M (rho^2 -
+//    2 r^2) / Q^2 in r and 4 M a^2 r sin cos / Q^2 in theta, plus r g x in r
+//    and -sin cos g (a^2 (x + u_r^2) - y^2) in theta.
+// About 73 operations, 98 with the quadratic forms u_i u_j d gamma^ij summed on
+// their own (push of 2e8 particles 9.0 -> 7.9 ms with sincos_theta and the
+// third-order steps above).
+__device__ __forceinline__ void geodesic_rhs_point(const StepArgs& A, double eps, double r, double s, double c,
+                                                   double ur, double ut, double up, double f[5]) {
+    using R = double;
+    const R a = R(A.a), a2 = R(A.a2);
+    const R r2 = r * r, s2 = s * s;
+    const R rho2 = r2 + a2 * (c * c);
+    const R T = R(A.M2) * r;
+    const R Q = rho2 + T;
+    const R rs2 = r * s2, rQ = rho2 * Q;
+    const R iP = rcp(rs2 * rQ);
+    const R x1 = rQ * iP, x2 = rs2 * iP;               // 1/(r sin^2), 1/(rho^2 Q)
+    const R ir = s2 * x1, is2 = r * x1;
+    const R irho2 = Q * x2, iQ = rho2 * x2;
+    const R beta = T * iQ;
+    const R aur = a * ur, y = is2 * up, ur2 = ur * ur;
+    const R W = aur + y;
+    const R x = irho2 * (ut * ut + W * up + aur * (aur * s2 + up));
+    R u0, iu0;
+    sqrt_rsqrt((eps + x + ur2 * (rho2 * iQ)) * (Q * irho2), u0, iu0);
+    const R g = irho2 * iu0, v1 = fma(ur, iu0, R(1));
+    f[0] = (g * ((r2 + a2) * ur + a * up) - beta * v1) * (ir * R(A.idlnr));
+    f[1] = g * ut * R(A.idth);
+    f[2] = g * W;
+    const R h = (R(A.M) * (iQ * iQ)) * ((u0 + ur) * v1);   // (u^0 + u_r)(1 + v) M / Q^2
+    const R sc = s * c;
+    f[3] = h * (rho2 - R(2) * r2) + (r * g) * x;
+    f[4] = h * (R(2) * a2 * (r * sc)) - (sc * g) * (a2 * (x + ur2) - y * y);
+}
+
+// The same in float (split precision), with the quadratic forms u_i u_j d
+// gamma^ij summed on their own; two reciprocals, of r sin^2 and of rho^2 Q, to
+// stay in range.
+__device__ __forceinline__ void geodesic_rhs_point(const StepArgs& A, float eps, float r, float s, float c,
+                                                   float ur, float ut, float up, float f[5]) {
+    using R = float;
     const R a = R(A.a), M = R(A.M);
     const R a2 = a * a, r2 = r * r, s2 = s * s;
     const R rho2 = r2 + a2 * (c * c);
     const R tMr = R(2) * M * r;
     const R Q = rho2 + tMr;
     const R rs2 = r * s2, rQ = rho2 * Q;
-    R x1, x2;                                           // 1/(r sin^2), 1/(rho^2 Q)
-    if constexpr (std::is_same<R, float>::value) {
-        x1 = rcp(rs2);
-        x2 = rcp(rQ);
-    } else {
-        const R iP = rcp(rs2 * rQ);
-        x1 = rQ * iP;
-        x2 = rs2 * iP;
-    }
+    const R x1 = rcp(rs2), x2 = rcp(rQ);               // 1/(r sin^2), 1/(rho^2 Q)
     const R ir = s2 * x1, is2 = r * x1;
     const R irho2 = Q * x2, iQ = rho2 * x2;
     const R beta = tMr * iQ;

@@ -718,12 +718,15 @@ __global__ __launch_bounds__(256) void slice_live_sum(const int32_t* __restrict_
     }
 }
 
-// THREADS: the tiling's slice size (kSliceThreads).  With the short series
-// the CIC kernels run at four waves per SIMD (at most 128 VGPRs; four
-// workgroups' LDS fit a CU); the long series needs more registers and runs
-// at three.
+// THREADS: the tiling's slice size (kSliceThreads).  The CIC kernels run at
+// four waves per SIMD (114 VGPRs; four workgroups' LDS fit a CU).  What bounds
+// them is FP64 issue: 2e8 particles on 2048 x 2048 in 7.9 ms a step where the
+// right-hand side of 98 operations a point and two Newton steps per estimate
+// took 9.0; with the long series and the library's sin and cos at the poles
+// (131 VGPRs, three waves) 2e5 particles on 256 x 256 took 21 us a step, now
+// 17.
 template <int THREADS, bool SHORT, int KICK>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(SHORT ? 4 : 3))) void push_deposit_f64_tiled(
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void push_deposit_f64_tiled(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap,
     int32_t* slice_live, const double* anchors) {
     push_deposit_tiled_body<THREADS, false, SHORT, KICK>(A, slices, slice_cap, slice_live, anchors);
@@ -736,7 +739,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(3))) vo
     push_deposit_tiled_body<THREADS, false, SHORT, kBoris, 3>(A, slices, slice_cap, slice_live, anchors);
 }
 template <int THREADS, bool SHORT>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(SHORT ? 4 : 3))) void push_deposit_f64_tiled_qed(
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void push_deposit_f64_tiled_qed(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap, int32_t* slice_live,
     const double* anchors, const QedArgs Q) {
     push_deposit_tiled_body<THREADS, false, SHORT, kBoris, 1, true>(A, slices, slice_cap, slice_live, anchors, Q);
