@@ -583,6 +583,29 @@ __device__ __forceinline__ double shape3(double x) {
     return a >= 2.0 ? 0.0 : (a >= 1.0 ? outer : inner);
 }
 
+// Its values at the four vertices around a point w in [0, 1) past the second
+// of them (those of shape3 at w + 1, w, w - 1, w - 2, without its selects).
+__device__ __forceinline__ void shape3_weights(double w, double o[4]) {
+    const double v = 1.0 - w, w2 = w * w, v2 = v * v;
+    o[0] = v2 * v * (1.0 / 6.0);
+    o[1] = fma(w2, fma(0.5, w, -1.0), 2.0 / 3.0);
+    o[2] = fma(v2, fma(0.5, v, -1.0), 2.0 / 3.0);
+    o[3] = w2 * w * (1.0 / 6.0);
+}
+
+// The weights of an end point x of a move on the five vertices of its window
+// along one direction, base the window's second vertex: x lies in the cell of
+// base or in the next one.
+__device__ __forceinline__ void window3_weights(double x, double base, double o[5]) {
+    const double f = floor(x);
+    double w[4];
+    shape3_weights(x - f, w);
+    const bool next = f > base;
+    o[0] = next ? 0.0 : w[0];
+    for (int a = 1; a < 4; ++a) o[a] = next ? w[a - 1] : w[a];
+    o[4] = next ? w[3] : 0.0;
+}
+
 // Columns beyond an axis fold onto their mirror (axisymmetry: (r, -theta,
 // phi) is (r, theta, phi + pi)).  Vertex columns keep the value (charge,
 // J^r, J^ph are even); theta-face columns (j + 1/2) change sign (J^th is
@@ -597,17 +620,15 @@ __device__ __forceinline__ int fold_face(int j, int nth, double& sign) {
 // (lower corner floor(min xi) - 1, floor(min eta) - 1) that holds both
 // supports, in the factorised form of the CIC version, folded across the
 // axes and handed to add(component, i, j, value): 20 F^r, 20 F^th, 25 G^ph.
-// The theta-direction weights are formed one window column at a time (the
-// F^th prefix sum runs along with them), so only the five r-direction
-// weights of each end point and their prefix sums stay live.
 template <class Add>
 __device__ __forceinline__ void esirkepov3(const Move& m, double idt, int nth, Add&& add) {
-    const int i0 = (int)floor(fmin(m.xi0, m.xi1)) - 1, j0 = (int)floor(fmin(m.eta0, m.eta1)) - 1;
-    double wx0[5], wx1[5];
-    for (int a = 0; a < 5; ++a) {
-        wx0[a] = shape3(m.xi0 - (double)(i0 + a));
-        wx1[a] = shape3(m.xi1 - (double)(i0 + a));
-    }
+    const double fi = floor(fmin(m.xi0, m.xi1)), fj = floor(fmin(m.eta0, m.eta1));
+    const int i0 = (int)fi - 1, j0 = (int)fj - 1;
+    double wx0[5], wx1[5], wy0[5], wy1[5];
+    window3_weights(m.xi0, fi, wx0);
+    window3_weights(m.xi1, fi, wx1);
+    window3_weights(m.eta0, fj, wy0);
+    window3_weights(m.eta1, fj, wy1);
     const double hf = -0.5 * m.qw * idt;
     const double cp6 = m.qw * m.dphi * idt * (1.0 / 6.0);
     double fx[4], runx = 0.0, runy = 0.0;
@@ -616,14 +637,13 @@ __device__ __forceinline__ void esirkepov3(const Move& m, double idt, int nth, A
         fx[a] = hf * runx;
     }
     for (int b = 0; b < 5; ++b) {
-        const double wy0 = shape3(m.eta0 - (double)(j0 + b)), wy1 = shape3(m.eta1 - (double)(j0 + b));
         const int jv = fold_vertex(j0 + b, nth);
-        const double sy = wy0 + wy1;
-        const double p1 = cp6 * fma(2.0, wy1, wy0), p0 = cp6 * fma(2.0, wy0, wy1);
+        const double sy = wy0[b] + wy1[b];
+        const double p1 = cp6 * fma(2.0, wy1[b], wy0[b]), p0 = cp6 * fma(2.0, wy0[b], wy1[b]);
         for (int a = 0; a < 4; ++a) add(0, i0 + a, jv, fx[a] * sy);
         for (int a = 0; a < 5; ++a) add(2, i0 + a, jv, fma(wx1[a], p1, wx0[a] * p0));
         if (b < 4) {
-            runy += wy1 - wy0;
+            runy += wy1[b] - wy0[b];
             const double fy = hf * runy;
             double sg;
             const int jf = fold_face(j0 + b, nth, sg);

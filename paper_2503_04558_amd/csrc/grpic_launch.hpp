@@ -29,7 +29,13 @@ constexpr int kSliceThreads = 256;
 // 96 gather loads per particle run markedly slower in four-wave slices
 // (measured: 5.0 against 2.8 ms for 2e7 particles on 2048^2).
 constexpr int kSliceThreads3 = 192;
-constexpr int kLaneGroups = 8;                             // lane permutation inside a slice
+// Lane permutation inside a slice: a wave's lanes take this many runs of
+// consecutive particles spread over the slice, so that its LDS adds rarely meet
+// at one address.  More runs cost the loads more lines: dense CIC slices are
+// fastest at 8 (2e8 particles: 175 ms per 20 steps, 177 at 16, 206 at 64), the
+// cubic shape, three times the adds, at 16 (2e7 particles: 1.60 ms a step, 1.86
+// at 8, 1.83 at 32).
+constexpr int kLaneGroups = 8, kLaneGroups3 = 16;
 constexpr int kMarginRows = 5;
 constexpr int kMarginCols = 4;
 constexpr int kWinRows = 2 * kMarginRows + 4;              // vertex rows of the LDS window

@@ -48,17 +48,20 @@ __device__ __forceinline__ double cic_f64(const double* __restrict__ F, const St
 // (xi - sr, eta - st) of the component's own stagger (guard rows and the
 // columns beyond the axes included; the grid has guard >= 3).
 __device__ __forceinline__ double spline3_f64(const double* __restrict__ F, const StepArgs& A, double f, double h) {
-    const int i = (int)floor(f), j = (int)floor(h);
+    const double ff = floor(f), fh = floor(h);
+    const int i = (int)ff, j = (int)fh;
     double wx[4], wy[4];
-    for (int a = 0; a < 4; ++a) {
-        wx[a] = shape3(f - (double)(i - 1 + a));
-        wy[a] = shape3(h - (double)(j - 1 + a));
-    }
+    shape3_weights(f - ff, wx);
+    shape3_weights(h - fh, wy);
     double sum = 0.0;
     for (int a = 0; a < 4; ++a) {
-        const uint32_t o = grid_index(A, i - 1 + a, j - 1);
-        double row = 0.0;
-        for (int b = 0; b < 4; ++b) row = fma(wy[b], *elem(F, o + (uint32_t)b), row);
+        const double* row4 = elem(F, grid_index(A, i - 1 + a, j - 1));
+        const double2_a8 lo = *reinterpret_cast<const double2_a8*>(row4);
+        const double2_a8 hi = *reinterpret_cast<const double2_a8*>(row4 + 2);
+        double row = fma(wy[0], lo.x, 0.0);
+        row = fma(wy[1], lo.y, row);
+        row = fma(wy[2], hi.x, row);
+        row = fma(wy[3], hi.y, row);
         sum = fma(wx[a], row, sum);
     }
     // an empty asm that takes the sum and clobbers memory: the next
@@ -506,7 +509,10 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
     // order after the deposit, so that consecutive lanes store consecutive
     // particles (the loads stay in the pushing lanes: staging them too would
     // make each wave wait for its loads before the first barrier)
-    constexpr int kStage = THREADS + THREADS / 32;
+    // (the cubic shape stores from the pushing lanes: without the 8.7 KB a
+    // fifth workgroup fits a CU)
+    constexpr bool kStaged = ORDER != 3;
+    constexpr int kStage = kStaged ? THREADS + THREADS / 32 : 1;
     __shared__ int st_cell[kStage];                       // new cell; -1: removed; -2: nothing to store
     __shared__ Elem<SPLIT> st_x[5][kStage];
     // the slice table is in dispatch order (XCD-aware bands, written so by
@@ -538,11 +544,12 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
     // the push).  Its state is loaded before the LDS set-up and the barrier
     // (which waits for LDS accesses only), so the loads overlap them.
     const int t = threadIdx.x;
-    const int run = (sl.len + kLaneGroups - 1) / kLaneGroups;
-    const int slot = (t % kLaneGroups) * run + t / kLaneGroups;
+    constexpr int kLanes = ORDER == 3 ? kLaneGroups3 : kLaneGroups;
+    const int run = (sl.len + kLanes - 1) / kLanes;
+    const int slot = (t % kLanes) * run + t / kLanes;
     const PIdx pi{sl.start, (uint32_t)slot};
     const int64_t p = sl.start + slot;
-    const bool mine = t / kLaneGroups < run && slot < sl.len && p < A.n;
+    const bool mine = t / kLanes < run && slot < sl.len && p < A.n;
     ParticleIn<Elem<SPLIT>> in;
     if (mine) in = load_particle<Elem<SPLIT>>(A, pi);
 
@@ -592,9 +599,13 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
         ParticleOut<Elem<SPLIT>> out;
         const bool dep = advance<SPLIT, SHORT, KICK, ORDER, QED>(A, pi, in, mv, ev, &tab, out);
         if constexpr (QED) qed_after_step(A, Q, in.s, *pi.at(Q.tag), *pi.at<double>(A.w), out, cr, qe);
-        const int si = slot + slot / 32;
-        st_cell[si] = out.kind == 2 ? out.cell : out.kind - 2;
-        for (int k = 0; k < 5; ++k) st_x[k][si] = out.x[k];
+        if constexpr (kStaged) {
+            const int si = slot + slot / 32;
+            st_cell[si] = out.kind == 2 ? out.cell : out.kind - 2;
+            for (int k = 0; k < 5; ++k) st_x[k][si] = out.x[k];
+        } else {
+            store_particle(A, pi, out);
+        }
         if (dep && mv.qw != 0.0) {                           // an uncharged move (a photon) adds only zeros
             if constexpr (ORDER == 3) {
                 // the cubic window: rows i3 .. i3 + 4, columns j3 .. j3 + 4
@@ -653,7 +664,7 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
     __syncthreads();
     // the new particle states, thread t storing slot t (before the flush, so
     // that the stores' latency overlaps it)
-    if (t < sl.len && sl.start + t < A.n) {
+    if (kStaged && t < sl.len && sl.start + t < A.n) {
         const int si = t + t / 32;
         ParticleOut<Elem<SPLIT>> o;
         const int sc = st_cell[si];
@@ -731,7 +742,12 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
     int32_t* slice_live, const double* anchors) {
     push_deposit_tiled_body<THREADS, false, SHORT, KICK>(A, slices, slice_cap, slice_live, anchors);
 }
-// The cubic shape's tiled kernel, at three or more waves per SIMD.
+// The cubic shape's tiled kernel.  What bounds it: LDS adds (65 a particle) and
+// the gather's latency (a component at a time), with five three-wave
+// workgroups per CU (127 VGPRs, 26.5 KB of LDS).  2e7 particles, 5 per cell, on
+// 2048 x 2048: 1.60 ms a step; 2.2 with the gather in 8-byte loads and weights
+// selected from |d| (136 VGPRs), the state staged in LDS (four workgroups) and
+// the CIC kernel's lane permutation.
 template <int THREADS, bool SHORT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64_tiled_spline3(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap, int32_t* slice_live,
