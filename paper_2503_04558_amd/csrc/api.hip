@@ -409,7 +409,11 @@ int grpic_push_deposit_qed(const grpic_metric* metric, const grpic_grid* grid,
     A.counters = reinterpret_cast<unsigned long long*>(counters);
     grpic::QedArgs Q;
     memset(&Q, 0, sizeof Q);
-    Q.gamma_thr = qed->gamma_thr;
+    // sqrt(x) > gamma_thr as a comparison of x: the smallest x for which it holds (sqrt is monotonic)
+    double x = qed->gamma_thr * qed->gamma_thr;
+    while (x > 0.0 && sqrt(nextafter(x, 0.0)) > qed->gamma_thr) x = nextafter(x, 0.0);
+    while (!(sqrt(x) > qed->gamma_thr)) x = nextafter(x, HUGE_VAL);
+    Q.emit_x = x;
     Q.eps_ph = qed->eps_ph;
     Q.P = 1.0 - exp(-qed->tau * dt);                          // eq. optical-depth
     Q.seed = qed->seed;

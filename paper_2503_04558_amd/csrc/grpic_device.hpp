@@ -174,8 +174,7 @@ constexpr double kTinyArg = 0.005;
 // instructions.
 constexpr double kPoleSin = 0.1;
 
-// SHORT selects the short series (a launch-uniform choice made once per
-// particle step, so that each variant is straight-line code).
+// SHORT selects the short series.
 template <bool SHORT, class R>
 __host__ __device__ __forceinline__ R exp_small(R x) {
     if constexpr (std::is_same<R, float>::value) {
@@ -251,12 +250,17 @@ __device__ __forceinline__ void anchor_values(const StepArgs& A, int ci, int cj,
     anchor_sc(A, cj, s, c);
 }
 
-template <class R>
+// How a launch evaluates points (StepArgs::small_steps, a template argument of
+// its kernel, so that each variant is straight-line code): by the library's
+// functions, or by the long or short Taylor series from an anchor.
+enum Series { kPlain = 0, kLong = 1, kShort = 2 };
+
+template <int SERIES, class R>
 __device__ __forceinline__ Anchor<R> make_anchor(const StepArgs& A, int ci, int cj) {
     Anchor<R> an;
     an.ci = ci;
     an.cj = cj;
-    if (A.small_steps) {
+    if constexpr (SERIES != kPlain) {
         double r, s, c;
         anchor_values(A, ci, cj, r, s, c);
         an.r = R(r);
@@ -269,13 +273,13 @@ __device__ __forceinline__ Anchor<R> make_anchor(const StepArgs& A, int ci, int 
 }
 
 // r, sin(theta), cos(theta) of the point (xi, eta) in grid units.
-template <bool SHORT, class R>
+template <int SERIES, class R>
 __device__ __forceinline__ void point_at(const StepArgs& A, const Anchor<R>& an, R xi, R eta, R& r, R& s, R& c) {
-    if (A.small_steps) {
-        r = an.r * exp_small<SHORT>((xi - R(an.ci)) * R(A.dlnr));
+    if constexpr (SERIES != kPlain) {
+        r = an.r * exp_small<SERIES == kShort>((xi - R(an.ci)) * R(A.dlnr));
         if (an.s >= R(kPoleSin)) {
             R sy, cy;
-            sincos_small<SHORT>((eta - R(an.cj)) * R(A.dth), sy, cy);
+            sincos_small<SERIES == kShort>((eta - R(an.cj)) * R(A.dth), sy, cy);
             s = fma(an.s, cy, an.c * sy);
             c = fma(an.c, cy, -(an.s * sy));
         } else {
@@ -283,28 +287,33 @@ __device__ __forceinline__ void point_at(const StepArgs& A, const Anchor<R>& an,
         }
     } else {
         r = exp(R(A.lnr0) + xi * R(A.dlnr));
-        sincos_theta(eta * R(A.dth), s, c);
+        const R th = eta * R(A.dth);
+        s = sin(th);
+        c = cos(th);
     }
 }
 
 // Same from offsets (dxi, deta) relative to the anchor cell's corner (the
 // split-precision path integrates positions this way: in float an absolute
 // xi near 2000 would carry an ulp of 1e-4 cells).
-template <bool SHORT, class R>
+template <int SERIES, class R>
 __device__ __forceinline__ void point_rel(const StepArgs& A, const Anchor<R>& an, R dxi, R deta, R& r, R& s, R& c) {
-    if (A.small_steps) {
-        r = an.r * exp_small<SHORT>(dxi * R(A.dlnr));
+    if constexpr (SERIES != kPlain) {
+        r = an.r * exp_small<SERIES == kShort>(dxi * R(A.dlnr));
         if (an.s >= R(kPoleSin)) {
             R sy, cy;
-            sincos_small<SHORT>(deta * R(A.dth), sy, cy);
+            sincos_small<SERIES == kShort>(deta * R(A.dth), sy, cy);
             s = fma(an.s, cy, an.c * sy);
             c = fma(an.c, cy, -(an.s * sy));
-            return;
+        } else {
+            sincos_theta((R(an.cj) + deta) * R(A.dth), s, c);
         }
     } else {
         r = exp(R(A.lnr0) + (R(an.ci) + dxi) * R(A.dlnr));
+        const R th = (R(an.cj) + deta) * R(A.dth);
+        s = sin(th);
+        c = cos(th);
     }
-    sincos_theta((R(an.cj) + deta) * R(A.dth), s, c);
 }
 
 // Geodesic right-hand side of eq. particle-eom (no Lorentz force) in grid
@@ -394,11 +403,11 @@ __device__ __forceinline__ void geodesic_rhs_point(const StepArgs& A, float eps,
 }
 
 // Same, evaluating the metric at (xi, eta) from the anchor.
-template <bool SHORT, class R>
+template <int SERIES, class R>
 __device__ __forceinline__ void geodesic_rhs(const StepArgs& A, const Anchor<R>& an, R eps, R xi, R eta,
                                              R ur, R ut, R up, R f[5]) {
     R r, s, c;
-    point_at<SHORT>(A, an, xi, eta, r, s, c);
+    point_at<SERIES>(A, an, xi, eta, r, s, c);
     geodesic_rhs_point(A, eps, r, s, c, ur, ut, up, f);
 }
 

@@ -33,7 +33,7 @@ struct QedStage {
 };
 
 struct QedArgs {
-    double gamma_thr, eps_ph, P;              // P = 1 - exp(-tau dt), formed on the host
+    double emit_x, eps_ph, P;                 // smallest x with sqrt(x) > gamma_thr; P = 1 - exp(-tau dt)
     uint64_t seed, step;
     int electron_sp, positron_sp, photon_sp;
     uint64_t* tag;
@@ -89,28 +89,30 @@ struct QedEvents {
 // Emission or conversion for a particle of species s, tag `tag`, weight w
 // whose step left it alive at cell / offsets / momenta `out` (kind 2, x =
 // xr, xth, u_r, u_th, u_ph).  Updates out (an emitter's recoil; a
-// converted photon becomes kind 1, removed) and fills cr.
-template <class Out>
+// converted photon becomes kind 1, removed) and fills cr.  point(i, j, xi, eta,
+// r, sin, cos) evaluates the point (xi, eta) of cell (i, j): from the tile's
+// anchors, as in the step (by the library's exp and sincos and two square
+// roots the test took a fifth of the step's instructions).
+template <class Out, class Point>
 __device__ __forceinline__ void qed_after_step(const StepArgs& A, const QedArgs& Q, int s, uint64_t tag, double w,
-                                               Out& out, Created& cr, QedEvents& qe) {
+                                               Out& out, Created& cr, QedEvents& qe, Point&& point) {
     cr.n = 0;
     if (out.kind != 2) return;
     const bool lepton = s == Q.electron_sp || s == Q.positron_sp;
     const bool photon = s == Q.photon_sp;
     if (!lepton && !photon) return;
-    // metric at the stored end point (cell corner + offsets), library functions
+    // metric at the stored end point (cell corner + offsets)
     const int i1 = div_by(out.cell, A.nth, A.inv_nth), j1 = out.cell - i1 * A.nth;
     const double xi = (double)i1 + out.x[0], eta = (double)j1 + out.x[1];
-    const double r = exp(A.lnr0 + xi * A.dlnr);
-    double sn, cs;
-    sincos(eta * A.dth, &sn, &cs);
+    double r, sn, cs;
+    point(i1, j1, xi, eta, r, sn, cs);
     Metric<double> k;
     ks_metric<double>(A.a, A.M, r, sn, cs, k);
     double u[3] = {out.x[2], out.x[3], out.x[4]};
     const double uu = k.h_rr * u[0] * u[0] + 2.0 * k.h_rp * u[0] * u[2] + k.h_tt * u[1] * u[1] + k.h_pp * u[2] * u[2];
-    const double umag = sqrt(uu);
-    const bool emits = lepton && sqrt(1.0 + uu) > Q.gamma_thr;
+    const bool emits = lepton && 1.0 + uu >= Q.emit_x;        // sqrt(1 + uu) > gamma_thr
     if (!emits && !photon) return;
+    const double umag = sqrt(uu);
     const Philox4 rn = philox4x64_10(tag, Q.step, 0ull, 0ull, Q.seed, 0ull);
     cr.cell = out.cell;
     cr.xr = out.x[0];

@@ -111,9 +111,9 @@ struct TileAnchors {
 static_assert(kSliceThreads >= 64 + kAnchorCols && kSliceThreads3 >= 64 + kAnchorCols,
               "waves 1 and 2 fill the anchor table's columns");
 
-template <class R>
+template <int SERIES, class R>
 __device__ __forceinline__ Anchor<R> anchor_for(const StepArgs& A, int ci, int cj, const TileAnchors* T) {
-    if (T && A.small_steps) {
+    if (T && SERIES != kPlain) {
         const int di = ci - T->i_lo, dj = cj - T->j_lo;
         if (di >= 0 && di < kAnchorRows && dj >= 0 && dj < kAnchorCols) {
             Anchor<R> an;
@@ -125,8 +125,19 @@ __device__ __forceinline__ Anchor<R> anchor_for(const StepArgs& A, int ci, int c
             return an;
         }
     }
-    return make_anchor<R>(A, ci, cj);
+    return make_anchor<SERIES, R>(A, ci, cj);
 }
+
+// r, sin, cos of a point of cell (i, j), from that cell's anchor.
+template <int SERIES>
+struct EndPoint {
+    const StepArgs& A;
+    const TileAnchors* T;
+    __device__ __forceinline__ void operator()(int i, int j, double xi, double eta, double& r, double& s,
+                                               double& c) const {
+        point_at<SERIES>(A, anchor_for<SERIES, double>(A, i, j, T), xi, eta, r, s, c);
+    }
+};
 
 // A particle's state as read at the start of a step (element type T: double,
 // or float in split precision); the weight is read by the step itself, after
@@ -190,9 +201,7 @@ __device__ __forceinline__ void store_particle(const StepArgs& A, const PIdx& p,
 // Advances live particle p by one step; its new state goes to out.  Returns
 // true when the move is to be deposited (mv filled), false when the particle
 // was or became removed without a deposit.
-// EARLY_QW: read the move's charge before the correctors (the monopole
-// kernel, whose emission test holds more values live, reads it at the end).
-template <bool SHORT, int KICK, int ORDER, bool EARLY_QW = true>
+template <int SERIES, int KICK, int ORDER>
 __device__ __forceinline__ bool advance_f64(const StepArgs& A, const PIdx& p, const ParticleIn<double>& in, Move& mv,
                                             Events& ev, const TileAnchors* T, ParticleOut<double>& out) {
     out.kind = 0;
@@ -225,14 +234,14 @@ __device__ __forceinline__ bool advance_f64(const StepArgs& A, const PIdx& p, co
     const double dt = A.dt;
     const double eps = massless ? 0.0 : 1.0;
     // one exp and one sincos per particle, at its start cell's corner
-    const Anchor<double> an = anchor_for<double>(A, ci, cj, T);
+    const Anchor<double> an = anchor_for<SERIES, double>(A, ci, cj, T);
     double f0[5], f1[5], yt[5];
     {
         // the kick takes the metric at x^n; the first RHS is evaluated from
         // r, sin, cos after it (the metric's derivatives and the six field
         // values are then never live together)
         double r0, s0, c0;
-        point_at<SHORT>(A, an, xi0, eta0, r0, s0, c0);
+        point_at<SERIES>(A, an, xi0, eta0, r0, s0, c0);
         Metric<double> k0;
         ks_metric<double>(A.a, A.M, r0, s0, c0, k0);
         if (!massless) kick<KICK>(k0, qm, dt, D, B, u);
@@ -246,11 +255,10 @@ __device__ __forceinline__ bool advance_f64(const StepArgs& A, const PIdx& p, co
     const double y0[5] = {xi0, eta0, 0.0, u[0], u[1]};
     // the move's charge q w, read here so that its loads complete during the
     // correctors (before the kick they would raise the register peak)
-    double qw = 0.0;
-    if constexpr (EARLY_QW) qw = A.q[s] * *p.at(w);
+    const double qw = A.q[s] * *p.at(w);
     for (int c = 0; c < 5; ++c) yt[c] = y0[c] + dt * f0[c];
     for (int it = 0; it < A.ncorr; ++it) {
-        geodesic_rhs<SHORT>(A, an, eps, yt[0], yt[1], yt[3], yt[4], u[2], f1);
+        geodesic_rhs<SERIES>(A, an, eps, yt[0], yt[1], yt[3], yt[4], u[2], f1);
         for (int c = 0; c < 5; ++c) yt[c] = y0[c] + 0.5 * dt * (f1[c] + f0[c]);
     }
     double xi1 = yt[0], eta1 = yt[1];
@@ -263,7 +271,6 @@ __device__ __forceinline__ bool advance_f64(const StepArgs& A, const PIdx& p, co
     }
     if (eta1 < 0.0) { eta1 = -eta1; u1t = -u1t; ev.refl = 1; }
     else if (eta1 > (double)A.nth) { eta1 = 2.0 * A.nth - eta1; u1t = -u1t; ev.refl = 1; }
-    if constexpr (!EARLY_QW) qw = A.q[s] * *p.at(w);
     mv = make_move(qw, xi0, eta0, xi1, eta1, yt[2]);
     if (A.phi) *p.at<double>(A.phi) += yt[2];
     if (xi1 < 0.0 || xi1 >= (double)A.nr) {
@@ -305,16 +312,16 @@ __device__ __forceinline__ float cic_f32(const float* __restrict__ F, const Step
 
 // Kick and predictor-corrector in precision R on offsets from the start
 // cell; y = (dxi, deta, phi, u_r, u_th) on return, u[2] = u_ph.
-template <bool SHORT, class R>
+template <int SERIES, class R>
 __device__ __forceinline__ void split_core(const StepArgs& A, int ci, int cj, R dxr, R dxt, R eps, R qm,
                                            bool massless, const R D[3], const R B[3], R u[3], R yt[5],
                                            const TileAnchors* T) {
-    const Anchor<R> an = anchor_for<R>(A, ci, cj, T);
+    const Anchor<R> an = anchor_for<SERIES, R>(A, ci, cj, T);
     const R dt = R(A.dt);
     R f0[5], f1[5];
     {
         R r0, s0, c0;
-        point_rel<SHORT>(A, an, dxr, dxt, r0, s0, c0);
+        point_rel<SERIES>(A, an, dxr, dxt, r0, s0, c0);
         Metric<R> k0;
         ks_metric<R>(R(A.a), R(A.M), r0, s0, c0, k0);
         if (!massless) boris_kick(k0, qm, dt, D, B, u);
@@ -329,7 +336,7 @@ __device__ __forceinline__ void split_core(const StepArgs& A, int ci, int cj, R 
     }
     for (int it = 0; it < A.ncorr; ++it) {
         R r, sn, cs;
-        point_rel<SHORT>(A, an, yt[0], yt[1], r, sn, cs);
+        point_rel<SERIES>(A, an, yt[0], yt[1], r, sn, cs);
         geodesic_rhs_point(A, eps, r, sn, cs, yt[3], yt[4], u[2], f1);
         for (int c = 0; c < 5; ++c) yt[c] = yh[c] + hdt * f1[c];
     }
@@ -341,7 +348,7 @@ __device__ __forceinline__ float offset_f32(double x) {
     return f < 1.0f ? f : 0.99999994f;
 }
 
-template <bool SHORT>
+template <int SERIES>
 __device__ __forceinline__ bool advance_split(const StepArgs& A, const PIdx& p, const ParticleIn<float>& in, Move& mv,
                                               Events& ev, const TileAnchors* T, ParticleOut<float>& out) {
     out.kind = 0;
@@ -370,12 +377,12 @@ __device__ __forceinline__ bool advance_split(const StepArgs& A, const PIdx& p, 
     if (fp64) {
         const double D[3] = {Df[0], Df[1], Df[2]}, B[3] = {Bf[0], Bf[1], Bf[2]};
         double u[3] = {in.u[0], in.u[1], in.u[2]};
-        split_core<SHORT, double>(A, ci, cj, (double)fxr, (double)fxt, massless ? 0.0 : 1.0, qm, massless, D, B, u, y, T);
+        split_core<SERIES, double>(A, ci, cj, (double)fxr, (double)fxt, massless ? 0.0 : 1.0, qm, massless, D, B, u, y, T);
         uph1 = u[2];
     } else {
         float u[3] = {in.u[0], in.u[1], in.u[2]};
         float yf[5];
-        split_core<SHORT, float>(A, ci, cj, fxr, fxt, massless ? 0.0f : 1.0f, (float)qm, massless, Df, Bf, u, yf, T);
+        split_core<SERIES, float>(A, ci, cj, fxr, fxt, massless ? 0.0f : 1.0f, (float)qm, massless, Df, Bf, u, yf, T);
         for (int c = 0; c < 5; ++c) y[c] = yf[c];
         uph1 = u[2];
     }
@@ -414,17 +421,16 @@ __device__ __forceinline__ bool advance_split(const StepArgs& A, const PIdx& p, 
 template <bool SPLIT>
 using Elem = typename std::conditional<SPLIT, float, double>::type;
 
-// SHORT: the short Taylor series, for grids fine enough for them
-// (small_steps == 2); the launch picks the kernel variant.
+// SERIES: how points are evaluated (A.small_steps); the launch picks the
+// kernel variant.
 // KICK: the momentum kick (kBoris, or kVay for the FP64 path only).
-// ORDER: the shape, 1 (CIC) or 3 (cubic spline, FP64 only).  QED: the
-// monopole step's kernels (the charge is read at the end there).
-template <bool SPLIT, bool SHORT, int KICK, int ORDER = 1, bool QED = false>
+// ORDER: the shape, 1 (CIC) or 3 (cubic spline, FP64 only).
+template <bool SPLIT, int SERIES, int KICK, int ORDER = 1>
 __device__ __forceinline__ bool advance(const StepArgs& A, const PIdx& p, const ParticleIn<Elem<SPLIT>>& in, Move& mv,
                                         Events& ev, const TileAnchors* T, ParticleOut<Elem<SPLIT>>& out) {
     static_assert(!SPLIT || (KICK == kBoris && ORDER == 1), "the split form runs the Boris kick and CIC only");
-    if constexpr (SPLIT) return advance_split<SHORT>(A, p, in, mv, ev, T, out);
-    else return advance_f64<SHORT, KICK, ORDER, !QED>(A, p, in, mv, ev, T, out);
+    if constexpr (SPLIT) return advance_split<SERIES>(A, p, in, mv, ev, T, out);
+    else return advance_f64<SERIES, KICK, ORDER>(A, p, in, mv, ev, T, out);
 }
 
 template <int ORDER = 1>
@@ -453,7 +459,7 @@ __device__ __forceinline__ void workgroup_events_to_global(const StepArgs& A, co
             if (cnt[k]) atomicAdd(A.counters + k, (unsigned long long)cnt[k]);
 }
 
-template <bool SPLIT, bool SHORT, int KICK, int ORDER = 1>
+template <bool SPLIT, int SERIES, int KICK, int ORDER = 1>
 __device__ __forceinline__ void push_deposit_body(const StepArgs& A) {
     __shared__ int cnt[5];
     if (threadIdx.x < 5) cnt[threadIdx.x] = 0;
@@ -464,7 +470,7 @@ __device__ __forceinline__ void push_deposit_body(const StepArgs& A) {
         Move mv;
         ParticleOut<Elem<SPLIT>> out;
         const bool dep =
-            advance<SPLIT, SHORT, KICK, ORDER>(A, pi, load_particle<Elem<SPLIT>>(A, pi), mv, ev, nullptr, out);
+            advance<SPLIT, SERIES, KICK, ORDER>(A, pi, load_particle<Elem<SPLIT>>(A, pi), mv, ev, nullptr, out);
         store_particle(A, pi, out);
         if (dep && mv.qw != 0.0) scatter_global<ORDER>(A, mv);   // an uncharged move adds only zeros
     }
@@ -475,25 +481,25 @@ __device__ __forceinline__ void push_deposit_body(const StepArgs& A) {
     workgroup_events_to_global(A, cnt);
 }
 
-template <bool SHORT, int KICK, int ORDER>
+template <int SERIES, int KICK, int ORDER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64(const StepArgs A) {
-    push_deposit_body<false, SHORT, KICK, ORDER>(A);
+    push_deposit_body<false, SERIES, KICK, ORDER>(A);
 }
 // The cubic shape's kernel (96 gather loads, a 5 x 5 deposit), at three
 // waves per SIMD like the CIC kernel (its gather loads one component at a
 // time).
-template <bool SHORT>
+template <int SERIES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64_spline3(const StepArgs A) {
-    push_deposit_body<false, SHORT, kBoris, 3>(A);
+    push_deposit_body<false, SERIES, kBoris, 3>(A);
 }
-template <bool SHORT>
+template <int SERIES>
 __global__ __launch_bounds__(256) void push_deposit_split(const StepArgs A) {
-    push_deposit_body<true, SHORT, kBoris>(A);
+    push_deposit_body<true, SERIES, kBoris>(A);
 }
 
 // QED: photon emission and pair conversion after the push (FP64, Boris,
 // CIC), with the created particles appended after the elements in use.
-template <int THREADS, bool SPLIT, bool SHORT, int KICK, int ORDER = 1, bool QED = false>
+template <int THREADS, bool SPLIT, int SERIES, int KICK, int ORDER = 1, bool QED = false>
 __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const Slice* __restrict__ slices,
                                                         int64_t slice_cap,
                                                         int32_t* __restrict__ slice_live,
@@ -569,7 +575,7 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
         touched[2] = kWinCols;
         touched[3] = -1;
     }
-    if (A.small_steps) {
+    if constexpr (SERIES != kPlain) {
         // table entry of row i is anchors[i + kMarginRows], of column j
         // S[j + kMarginCols] and C[j + kMarginCols]
         const double* S = anchors + (A.nr + 2 * kMarginRows);
@@ -597,8 +603,9 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
     if (mine) {
         Move mv;
         ParticleOut<Elem<SPLIT>> out;
-        const bool dep = advance<SPLIT, SHORT, KICK, ORDER, QED>(A, pi, in, mv, ev, &tab, out);
-        if constexpr (QED) qed_after_step(A, Q, in.s, *pi.at(Q.tag), *pi.at<double>(A.w), out, cr, qe);
+        const bool dep = advance<SPLIT, SERIES, KICK, ORDER>(A, pi, in, mv, ev, &tab, out);
+        if constexpr (QED)
+            qed_after_step(A, Q, in.s, *pi.at(Q.tag), *pi.at<double>(A.w), out, cr, qe, EndPoint<SERIES>{A, &tab});
         if constexpr (kStaged) {
             const int si = slot + slot / 32;
             st_cell[si] = out.kind == 2 ? out.cell : out.kind - 2;
@@ -736,11 +743,11 @@ __global__ __launch_bounds__(256) void slice_live_sum(const int32_t* __restrict_
 // took 9.0; with the long series and the library's sin and cos at the poles
 // (131 VGPRs, three waves) 2e5 particles on 256 x 256 took 21 us a step, now
 // 17.
-template <int THREADS, bool SHORT, int KICK>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void push_deposit_f64_tiled(
+template <int THREADS, int SERIES, int KICK>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(SERIES == kPlain ? 3 : 4))) void push_deposit_f64_tiled(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap,
     int32_t* slice_live, const double* anchors) {
-    push_deposit_tiled_body<THREADS, false, SHORT, KICK>(A, slices, slice_cap, slice_live, anchors);
+    push_deposit_tiled_body<THREADS, false, SERIES, KICK>(A, slices, slice_cap, slice_live, anchors);
 }
 // The cubic shape's tiled kernel.  What bounds it: LDS adds (65 a particle) and
 // the gather's latency (a component at a time), with five three-wave
@@ -748,22 +755,22 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
 // 2048 x 2048: 1.60 ms a step; 2.2 with the gather in 8-byte loads and weights
 // selected from |d| (136 VGPRs), the state staged in LDS (four workgroups) and
 // the CIC kernel's lane permutation.
-template <int THREADS, bool SHORT>
+template <int THREADS, int SERIES>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64_tiled_spline3(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap, int32_t* slice_live,
     const double* anchors) {
-    push_deposit_tiled_body<THREADS, false, SHORT, kBoris, 3>(A, slices, slice_cap, slice_live, anchors);
+    push_deposit_tiled_body<THREADS, false, SERIES, kBoris, 3>(A, slices, slice_cap, slice_live, anchors);
 }
-template <int THREADS, bool SHORT>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void push_deposit_f64_tiled_qed(
+template <int THREADS, int SERIES>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(SERIES == kPlain ? 3 : 4))) void push_deposit_f64_tiled_qed(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap, int32_t* slice_live,
     const double* anchors, const QedArgs Q) {
-    push_deposit_tiled_body<THREADS, false, SHORT, kBoris, 1, true>(A, slices, slice_cap, slice_live, anchors, Q);
+    push_deposit_tiled_body<THREADS, false, SERIES, kBoris, 1, true>(A, slices, slice_cap, slice_live, anchors, Q);
 }
 
 // The QED step of one block of particles b .. b + 255 below `end`: one
 // particle per thread, global atomics.
-template <bool SHORT>
+template <int SERIES>
 __device__ __forceinline__ void qed_block(const StepArgs& A, const QedArgs& Q, int64_t b, int64_t end, int* cnt) {
     if (threadIdx.x < 5) cnt[threadIdx.x] = 0;
     const PIdx pi{b, threadIdx.x};
@@ -775,8 +782,8 @@ __device__ __forceinline__ void qed_block(const StepArgs& A, const QedArgs& Q, i
         Move mv;
         ParticleOut<double> out;
         const ParticleIn<double> in = load_particle<double>(A, pi);
-        const bool dep = advance<false, SHORT, kBoris, 1, true>(A, pi, in, mv, ev, nullptr, out);
-        qed_after_step(A, Q, in.s, *pi.at(Q.tag), *pi.at<double>(A.w), out, cr, qe);
+        const bool dep = advance<false, SERIES, kBoris>(A, pi, in, mv, ev, nullptr, out);
+        qed_after_step(A, Q, in.s, *pi.at(Q.tag), *pi.at<double>(A.w), out, cr, qe, EndPoint<SERIES>{A, nullptr});
         store_particle(A, pi, out);
         if (dep && mv.qw != 0.0) scatter_global(A, mv);
     }
@@ -792,26 +799,26 @@ __device__ __forceinline__ void qed_block(const StepArgs& A, const QedArgs& Q, i
 // Without a tiling: block b takes particles 256 b .. 256 b + 255 of those in
 // use (the grid covers the capacity; blocks beyond the elements in use
 // return at once).
-template <bool SHORT>
+template <int SERIES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64_qed(
     const StepArgs A, const QedArgs Q) {
     __shared__ int cnt[5];
     const int64_t end = Q.n_used[0];
     const int64_t b = (int64_t)blockIdx.x * blockDim.x;
     if (b >= end) return;
-    qed_block<SHORT>(A, Q, b, end, cnt);
+    qed_block<SERIES>(A, Q, b, end, cnt);
 }
 
 // With a tiling: the particles appended since the sort, [n_sorted,
 // n_used[0]), which no slice covers; a few blocks loop over them (a short
 // range, so the loop's register spills cost little).
-template <bool SHORT>
+template <int SERIES>
 __global__ __launch_bounds__(256) void push_deposit_f64_qed_tail(const StepArgs A, const QedArgs Q) {
     __shared__ int cnt[5];
     const int64_t end = Q.n_used[0];
     const int64_t start = min(*Q.tail_start, end);
     for (int64_t b = start + (int64_t)blockIdx.x * blockDim.x; b < end; b += (int64_t)gridDim.x * blockDim.x) {
-        qed_block<SHORT>(A, Q, b, end, cnt);
+        qed_block<SERIES>(A, Q, b, end, cnt);
         __syncthreads();                                    // cnt is cleared again next pass
     }
 }
@@ -909,11 +916,11 @@ inline QedLayout qed_layout(int64_t slices) {
 
 size_t qed_workspace_bytes(int64_t slice_cap) { return qed_layout(slice_cap).total; }
 
-template <int THREADS, bool SHORT>
+template <int THREADS, int SERIES>
 __global__ __launch_bounds__(THREADS) void push_deposit_split_tiled(const StepArgs A, const Slice* __restrict__ slices,
                                                                     int64_t slice_cap, int32_t* slice_live,
                                                                     const double* anchors) {
-    push_deposit_tiled_body<THREADS, true, SHORT, kBoris>(A, slices, slice_cap, slice_live, anchors);
+    push_deposit_tiled_body<THREADS, true, SERIES, kBoris>(A, slices, slice_cap, slice_live, anchors);
 }
 
 // Q_ij += q w S_ij(x_p) over live particles (FP64 or split offsets).
@@ -958,27 +965,33 @@ __global__ __launch_bounds__(256) void charge3_kernel(const StepArgs A, double* 
 
 static inline dim3 blocks_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
+// f(integral constant of the launch's series).
+template <class F>
+static void with_series(const StepArgs& A, F&& f) {
+    if (A.small_steps == kShort) f(std::integral_constant<int, kShort>{});
+    else if (A.small_steps == kLong) f(std::integral_constant<int, kLong>{});
+    else f(std::integral_constant<int, kPlain>{});
+}
+
+// Particles in any order.  Sets that leave CUs without a 256-lane workgroup
+// run one-wave ones, so that they spread over all CUs (the step is one long
+// dependent chain per wave: 2e4 particles 16.0 -> 14.2 us).
 hipError_t launch_push_deposit(const StepArgs& A, bool split, hipStream_t stream, int kick, int order) {
     if (A.n <= 0) return hipSuccess;
-    const bool sh = A.small_steps == 2;
-    const dim3 g = blocks_for(A.n), b(256);
-    if (order == 3) {                                    // FP64, Boris kick (checked by the caller)
-        if (sh) hipLaunchKernelGGL(push_deposit_f64_spline3<true>, g, b, 0, stream, A);
-        else hipLaunchKernelGGL(push_deposit_f64_spline3<false>, g, b, 0, stream, A);
-        return hipGetLastError();
-    }
-    if (split && sh) hipLaunchKernelGGL(push_deposit_split<true>, g, b, 0, stream, A);
-    else if (split) hipLaunchKernelGGL(push_deposit_split<false>, g, b, 0, stream, A);
-    else if (kick == kVay && sh) hipLaunchKernelGGL((push_deposit_f64<true, kVay, 1>), g, b, 0, stream, A);
-    else if (kick == kVay) hipLaunchKernelGGL((push_deposit_f64<false, kVay, 1>), g, b, 0, stream, A);
-    else if (sh) hipLaunchKernelGGL((push_deposit_f64<true, kBoris, 1>), g, b, 0, stream, A);
-    else hipLaunchKernelGGL((push_deposit_f64<false, kBoris, 1>), g, b, 0, stream, A);
+    const unsigned threads = A.n <= 256 * 256 ? 64 : 256;
+    const dim3 g((unsigned)((A.n + threads - 1) / threads)), b(threads);
+    with_series(A, [&](auto sr) {
+        constexpr int S = decltype(sr)::value;
+        if (order == 3) hipLaunchKernelGGL(push_deposit_f64_spline3<S>, g, b, 0, stream, A);   // FP64, Boris kick (checked by the caller)
+        else if (split) hipLaunchKernelGGL(push_deposit_split<S>, g, b, 0, stream, A);
+        else if (kick == kVay) hipLaunchKernelGGL((push_deposit_f64<S, kVay, 1>), g, b, 0, stream, A);
+        else hipLaunchKernelGGL((push_deposit_f64<S, kBoris, 1>), g, b, 0, stream, A);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_push_deposit_qed(const StepArgs& A, QedArgs Q, void* tiling, int64_t slice_cap, void* ws,
                                    hipStream_t stream) {
-    const bool sh = A.small_steps == 2;
     Q.tail_start = nullptr;
     Q.staged = 0;
     if (tiling) {
@@ -1008,28 +1021,30 @@ hipError_t launch_push_deposit_qed(const StepArgs& A, QedArgs Q, void* tiling, i
         const double* anchors = tiling_at<const double>(tiling, L.anchors);   // written by the sort
         const dim3 g((unsigned)((slice_cap + 7) / 8 * 8));
         const dim3 b(kSliceThreads);
-        if (sh) hipLaunchKernelGGL((push_deposit_f64_tiled_qed<kSliceThreads, true>), g, b, 0, stream, A, slices,
-                                   slice_cap, live, anchors, Q);
-        else hipLaunchKernelGGL((push_deposit_f64_tiled_qed<kSliceThreads, false>), g, b, 0, stream, A, slices,
-                                slice_cap, live, anchors, Q);
+        with_series(A, [&](auto sr) {
+            hipLaunchKernelGGL((push_deposit_f64_tiled_qed<kSliceThreads, decltype(sr)::value>), g, b, 0, stream, A,
+                               slices, slice_cap, live, anchors, Q);
+        });
         if (A.counters)
             hipLaunchKernelGGL(slice_live_sum, dim3(64), dim3(256), 0, stream, live, slice_cap, A.counters);
     }
     if (tiling) {                                        // the particles appended since the sort
         const dim3 g((unsigned)std::min<int64_t>((A.n + 255) / 256, 1024));
-        if (sh) hipLaunchKernelGGL(push_deposit_f64_qed_tail<true>, g, dim3(256), 0, stream, A, Q);
-        else hipLaunchKernelGGL(push_deposit_f64_qed_tail<false>, g, dim3(256), 0, stream, A, Q);
+        with_series(A, [&](auto sr) {
+            hipLaunchKernelGGL(push_deposit_f64_qed_tail<decltype(sr)::value>, g, dim3(256), 0, stream, A, Q);
+        });
     } else {                                             // every element in use
         const dim3 g((unsigned)((A.n + 255) / 256));
-        if (sh) hipLaunchKernelGGL(push_deposit_f64_qed<true>, g, dim3(256), 0, stream, A, Q);
-        else hipLaunchKernelGGL(push_deposit_f64_qed<false>, g, dim3(256), 0, stream, A, Q);
+        with_series(A, [&](auto sr) {
+            hipLaunchKernelGGL(push_deposit_f64_qed<decltype(sr)::value>, g, dim3(256), 0, stream, A, Q);
+        });
     }
     if (Q.staged) {                                      // place the staged particles after all others
         scan_exclusive(Q.st.count, slice_cap + 1, Q.st.blocksums, stream);
         const int64_t threads = slice_cap * kQedStage;
         hipLaunchKernelGGL(qed_place, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, A, Q);
         if (Q.qcounters)
-            hipLaunchKernelGGL(qed_event_sum, dim3(64), dim3(256), 0, stream, Q.st.ev, slice_cap, Q.qcounters);
+            hipLaunchKernelGGL(qed_event_sum, dim3(256), dim3(256), 0, stream, Q.st.ev, slice_cap, Q.qcounters);
     }
     hipLaunchKernelGGL(qed_end, dim3(1), dim3(1), 0, stream, Q.n_used, Q.cap,
                        Q.staged ? Q.st.count + slice_cap : nullptr);
@@ -1043,41 +1058,27 @@ hipError_t launch_push_deposit_tiled(const StepArgs& A, bool split, void* tiling
     if (A.n <= 0) return hipSuccess;
     const TilingLayout L = tiling_layout(A.n, A.nr, A.nth);
     const double* anchors = tiling_at<const double>(tiling, L.anchors);   // written by the sort
-    const bool sh = A.small_steps == 2;
     const bool cubic = order == 3;                       // FP64, Boris kick (checked by the caller)
     const int64_t cap = cubic ? L.cap3 : L.cap;
     const Slice* slices = tiling_at<const Slice>(tiling, cubic ? L.slices3 : L.slices);
     int32_t* live = tiling_at<int32_t>(tiling, cubic ? L.live3 : L.live);
     const dim3 g((unsigned)((cap + 7) / 8 * 8));
-    if (cubic) {
-        const dim3 b(kSliceThreads3);
-        if (sh)
-            hipLaunchKernelGGL((push_deposit_f64_tiled_spline3<kSliceThreads3, true>), g, b, 0, stream, A, slices, cap,
+    const dim3 b(cubic ? kSliceThreads3 : kSliceThreads);
+    with_series(A, [&](auto sr) {
+        constexpr int S = decltype(sr)::value;
+        if (cubic)
+            hipLaunchKernelGGL((push_deposit_f64_tiled_spline3<kSliceThreads3, S>), g, b, 0, stream, A, slices, cap,
                                live, anchors);
-        else
-            hipLaunchKernelGGL((push_deposit_f64_tiled_spline3<kSliceThreads3, false>), g, b, 0, stream, A, slices,
-                               cap, live, anchors);
-    } else {
-        const dim3 b(kSliceThreads);
-        if (split && sh)
-            hipLaunchKernelGGL((push_deposit_split_tiled<kSliceThreads, true>), g, b, 0, stream, A, slices, cap, live,
-                               anchors);
         else if (split)
-            hipLaunchKernelGGL((push_deposit_split_tiled<kSliceThreads, false>), g, b, 0, stream, A, slices, cap, live,
+            hipLaunchKernelGGL((push_deposit_split_tiled<kSliceThreads, S>), g, b, 0, stream, A, slices, cap, live,
                                anchors);
-        else if (kick == kVay && sh)
-            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, true, kVay>), g, b, 0, stream, A, slices, cap,
-                               live, anchors);
         else if (kick == kVay)
-            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, false, kVay>), g, b, 0, stream, A, slices, cap,
-                               live, anchors);
-        else if (sh)
-            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, true, kBoris>), g, b, 0, stream, A, slices, cap,
-                               live, anchors);
+            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, S, kVay>), g, b, 0, stream, A, slices, cap, live,
+                               anchors);
         else
-            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, false, kBoris>), g, b, 0, stream, A, slices, cap,
+            hipLaunchKernelGGL((push_deposit_f64_tiled<kSliceThreads, S, kBoris>), g, b, 0, stream, A, slices, cap,
                                live, anchors);
-    }
+    });
     if (A.counters)
         hipLaunchKernelGGL(slice_live_sum, dim3(256), dim3(256), 0, stream, live, cap, A.counters);
     return hipGetLastError();
