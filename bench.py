@@ -252,14 +252,22 @@ def run_adjoint(args):
             "dense_lambda_bwd_ms": min(bd), "dense_lambda_bwd_over_fwd": min(bd) / min(f_ck)}
 
 
-# Field step: grid planes one evaluation must move at least, with the
-# metric coefficients formed in registers, the six inverse areas tabulated
-# and the corrector's constant part R = X^n + dt (w0 C(X^n) - J) formed once:
-# the predictor reads the state, inverse areas and currents (3) and writes
-# the predicted state and R; a corrector pass reads the iterate, R and the
-# inverse areas and writes the iterate.
+# Field step: grid planes that it must move at least, with the metric
+# coefficients formed in registers, the six inverse areas tabulated and the
+# corrector's constant part R = X^n + dt (w0 C(X^n) - J) formed once.  A launch
+# carries up to four passes (predictor and correctors) over one read of its
+# inputs, a step has at least two launches: the first reads the state, inverse
+# areas and currents (3) and writes the iterate and R, a later one reads the
+# iterate, R and the inverse areas and writes the iterate.  CORRECTOR is the
+# later launches' share of one of the default step's 7 correctors.
 FIELD_PLANES_PREDICTOR = 6 + 6 + 3 + 6 + 6
-FIELD_PLANES_CORRECTOR = 6 + 6 + 6 + 6
+FIELD_PLANES_LATER_LAUNCH = 6 + 6 + 6 + 6
+FIELD_PLANES_CORRECTOR = FIELD_PLANES_LATER_LAUNCH / 7
+
+
+def field_planes(ncorr: int) -> int:
+    launches = max(2, (ncorr + 1 + 3) // 4)
+    return FIELD_PLANES_PREDICTOR + (launches - 1) * FIELD_PLANES_LATER_LAUNCH
 
 
 def run_fields(args, g, F):
@@ -289,7 +297,7 @@ def run_fields(args, g, F):
     ms = e0.elapsed_time(e1) / args.field_steps
     finite = all(bool(torch.isfinite(s).all()) for s in state)
     plane = (g.nr + 1) * (g.nth + 1) * 8
-    nbytes = plane * (FIELD_PLANES_PREDICTOR + args.field_ncorr * FIELD_PLANES_CORRECTOR)
+    nbytes = plane * field_planes(args.field_ncorr)
     gbs = nbytes / (ms * 1e-3) / 1e9
     log(f"fields: {args.field_steps} steps of ncorr={args.field_ncorr}: {ms:.3f} ms/step, finite={finite}")
     return {"grid": [g.nr, g.nth], "ncorr": args.field_ncorr, "w1": args.field_w1, "steps": args.field_steps,

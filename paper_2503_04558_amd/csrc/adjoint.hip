@@ -97,9 +97,9 @@ __global__ __launch_bounds__(128) void lam_prefix(const BackArgs B, const int* _
 // at the end: a particle stays in a cell for a few steps, so this takes a
 // few times fewer global atomics than adding every step.
 //
-// What bounds the sweep: FP64 issue, 64 % of the time with two waves per SIMD
+// What bounds the sweep: FP64 issue, 61 % of the time with two waves per SIMD
 // (255 VGPRs; 1e6 particles x 32 steps with a dense lambda on 512 x 512 in
-// 4.9 ms, 1.66e9 VALU instructions; at one wave per SIMD 6.7 ms; with a tape
+// 4.9 ms, 1.63e9 VALU instructions; at one wave per SIMD 6.7 ms; with a tape
 // that spilled to scratch 15 GB of traffic and 7.3 ms).  A workgroup is one
 // wave (nothing is shared between its particles), so that small sets spread
 // over the CUs: 20 KB of LDS each, eight per CU.  Workgroup b, on XCD b % 8,

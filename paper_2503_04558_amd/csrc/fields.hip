@@ -110,10 +110,10 @@ __global__ __launch_bounds__(256) void field_tables_kernel(FieldArgs F, Quad Q) 
 // formed once per pass (a tile with a halo formed each four times over).
 //
 // Measured, predictor and 7 correctors on 2048 x 2048: 500 us in two launches
-// of four passes, 0.87 GB of HBM traffic each, where one launch per pass took
-// 1560 us (0.82 to 1.12 GB each, 8 launches and 3 for the edges).  What bounds
-// it now is the marching step's latency: the waves of a workgroup meet at a
-// barrier each row, FP64 issue fills 45 % of the time and HBM runs at 3.5
+// of four passes, 0.96 and 0.87 GB of HBM traffic, where one launch per pass
+// took 1560 us (0.82 to 1.12 GB each, 8 launches and 3 for the edges).  What
+// bounds it now is the marching step's latency: the waves of a workgroup meet
+// at a barrier each row, VALU issue fills half of the time and HBM runs at 3.7
 // TB/s.  Three passes per launch: 870 us, two: 810 (without the second strip,
 // which gave 685 for four); R and the areas re-read by each pass instead of
 // kept in LDS: 1.58 GB per launch, 765 us.

@@ -56,13 +56,17 @@ __global__ __launch_bounds__(256) void sort_setup(const SortArgs S, int64_t len,
 
 // Chunk of consecutive particles per histogram / scatter workgroup, and the
 // LDS hash table that counts its cells: at most half full, so an empty slot
-// is always found.  A scatter workgroup waits once for its cells' atomics
-// (with return, at the memory side) and writes a run per distinct cell;
-// 2048-particle chunks halve both per particle and beat 1024 (scatter of a
-// drifted 2e8 6.4 against 8.1 ms; 2e7 particles at 5 per cell, drifted by
-// several rows, 1.20 against 1.34 ms).  Chunks dealt to the XCDs in bands
-// (neighbouring ones through one L2) write slower: 7.9 ms.  A slot's 8 bytes hold its cell and count and then, in the
-// scatter, the cell's reserved output index.
+// is always found.  A scatter workgroup waits for its cells' atomics (with
+// return, at the memory side) and writes a run per distinct cell; both are per
+// chunk, and 2048-particle chunks beat 1024 (scatter of a drifted 2e8 5.8
+// against 7.2 ms; 2e7 particles at 5 per cell, drifted by several rows, 1.20
+// against 1.34 ms).  What bounds the scatter is the memory side, where chunks
+// meet on the counters' lines: a thread's 16 atomics in flight together instead
+// of one after another, 1.20 -> 1.45 ms; the particles exchanged through LDS
+// and written in cell order, 1.20 -> 1.23 ms; chunks dealt to the XCDs in bands
+// (neighbouring ones through one L2), 5.8 -> 7.0 ms for 2e8.  A slot's 8 bytes
+// hold its cell and count and then, in the scatter, the cell's reserved output
+// index.
 constexpr int kChunkThreads = 256;
 constexpr int kChunkItems = 8;
 constexpr int kChunk = kChunkThreads * kChunkItems;
