@@ -186,7 +186,7 @@ struct ParticleOut {
     T x[5];
 };
 
-template <class T>
+template <class T, bool UPH = true>
 __device__ __forceinline__ void store_particle(const StepArgs& A, const PIdx& p, const ParticleOut<T>& o) {
     if (o.kind == 0) return;
     *p.at(A.cell) = o.kind == 2 ? o.cell : -1;
@@ -195,7 +195,7 @@ __device__ __forceinline__ void store_particle(const StepArgs& A, const PIdx& p,
     *p.at<T>(A.xth) = o.x[1];
     *p.at<T>(A.ur) = o.x[2];
     *p.at<T>(A.uth) = o.x[3];
-    *p.at<T>(A.uph) = o.x[4];
+    if constexpr (UPH) *p.at<T>(A.uph) = o.x[4];
 }
 
 // Advances live particle p by one step; its new state goes to out.  Returns
@@ -520,7 +520,10 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
     constexpr bool kStaged = ORDER != 3;
     constexpr int kStage = kStaged ? THREADS + THREADS / 32 : 1;
     __shared__ int st_cell[kStage];                       // new cell; -1: removed; -2: nothing to store
-    __shared__ Elem<SPLIT> st_x[5][kStage];
+    // (the split form stages four of its five floats and stores u_ph from the
+    // pushing lanes: 31,792 B instead of 32,848, and a fifth workgroup fits)
+    constexpr int kStageX = SPLIT ? 4 : 5;
+    __shared__ Elem<SPLIT> st_x[kStageX][kStage];
     // the slice table is in dispatch order (XCD-aware bands, written so by
     // the sort): one load finds this workgroup's slice
     const int64_t logical = blockIdx.x;
@@ -609,7 +612,9 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
         if constexpr (kStaged) {
             const int si = slot + slot / 32;
             st_cell[si] = out.kind == 2 ? out.cell : out.kind - 2;
-            for (int k = 0; k < 5; ++k) st_x[k][si] = out.x[k];
+            for (int k = 0; k < kStageX; ++k) st_x[k][si] = out.x[k];
+            if constexpr (SPLIT)
+                if (out.kind == 2) *pi.at<Elem<SPLIT>>(A.uph) = out.x[4];
         } else {
             store_particle(A, pi, out);
         }
@@ -677,8 +682,8 @@ __device__ __forceinline__ void push_deposit_tiled_body(const StepArgs& A, const
         const int sc = st_cell[si];
         o.kind = sc >= 0 ? 2 : sc + 2;
         o.cell = sc;
-        for (int k = 0; k < 5; ++k) o.x[k] = st_x[k][si];
-        store_particle(A, PIdx{sl.start, (uint32_t)t}, o);
+        for (int k = 0; k < kStageX; ++k) o.x[k] = st_x[k][si];
+        store_particle<Elem<SPLIT>, !SPLIT>(A, PIdx{sl.start, (uint32_t)t}, o);
     }
     // flush the window's non-zero entries that lie inside the grid arrays
     double* const J[3] = {A.Fr, A.Fth, A.Gph};
@@ -916,6 +921,10 @@ inline QedLayout qed_layout(int64_t slices) {
 
 size_t qed_workspace_bytes(int64_t slice_cap) { return qed_layout(slice_cap).total; }
 
+// The split form's tiled kernel: VALU issue and waits for loads and LDS, at five
+// waves per SIMD (91 VGPRs; 31.8 KB of LDS, five workgroups per CU): 2e8
+// particles on 4096 x 4096 in 7.7 ms a step, 8.3 at four; with no state staged
+// at all, every store from the pushing lanes, 7.8.
 template <int THREADS, int SERIES>
 __global__ __launch_bounds__(THREADS) void push_deposit_split_tiled(const StepArgs A, const Slice* __restrict__ slices,
                                                                     int64_t slice_cap, int32_t* slice_live,
