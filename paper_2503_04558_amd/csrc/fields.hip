@@ -198,11 +198,12 @@ struct MarchState {
 // the theta basis vector is reversed) a component there is its value at the
 // mirrored location, negated for D^th and B^th: integer columns -m <-> m and
 // nth + m <-> nth - m, columns at j + 1/2 (D^th, B^r, B^ph) -m <-> m - 1 and
-// nth - 1 + m <-> nth - m, m = 1 .. guard (nth > guard).
+// nth - 1 + m <-> nth - m, m = 1 .. guard (nth > guard); each is stored by the
+// lane of its mirror image (mirrors: this strip stores some).
 // Rows between the edges, which are nearly all, take no loop: this wave's
 // rows are what the others wait for.
 __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs& out, const StageArgs& S, int r, int j,
-                                            int lane, bool owned, bool first_strip, bool last_strip, double v[6]) {
+                                            int lane, bool owned, bool mirrors, bool last_strip, double v[6]) {
     const int L = S.damp_cells;
     if (L > 0 && r >= F.nr - L - 1) {                   // damping at x = r, r + 1/2
         const double x_in = (double)(F.nr - L);
@@ -214,11 +215,13 @@ __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs&
         for (int c = 0; c < 6; ++c) v[c] *= c == 0 || c > 3 ? f_h : f_i;
     }
     const int fm = F.nth - j;
-    // row q of component c, with its mirrored columns
+    // row q of component c, and its mirrored columns
     auto put = [&](int c, int q) {
         const bool chalf = c == 1 || c == 3 || c == 5;
         if (owned && !(chalf && fm == 0)) *elem(out.c[c], F.at(q, j)) = v[c];   // (a mirrored column there)
-        if (!first_strip && !last_strip) return;
+    };
+    auto mirror = [&](int c, int q) {
+        const bool chalf = c == 1 || c == 3 || c == 5;
         const double mir = (c == 1 || c == 4) ? -v[c] : v[c];
         const int near = chalf ? -j - 1 : -j;
         if (owned && near < 0 && near >= -F.guard) *elem(out.c[c], F.at(q, near)) = mir;
@@ -226,6 +229,8 @@ __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs&
     };
     if (r > 0 && r < F.nr - 1) {
         for (int c = 0; c < 6; ++c) put(c, r);
+        if (mirrors)
+            for (int c = 0; c < 6; ++c) mirror(c, r);
         return;
     }
     for (int c = 0; c < 6; ++c) {
@@ -233,7 +238,10 @@ __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs&
         const int top = half ? F.nr - 1 : F.nr;
         if (r > top) continue;
         const int lo = r == 0 ? -F.guard : r, hi = r == top ? F.nr + F.guard : r;
-        for (int q = lo; q <= hi; ++q) put(c, q);
+        for (int q = lo; q <= hi; ++q) {
+            put(c, q);
+            if (mirrors) mirror(c, q);
+        }
         // the guard rows' columns beyond the mirrored ones repeat the edge row's
         if (last_strip && lo < hi)
             for (int p = F.nth + F.guard + (chalf ? 0 : 1) + lane; p < F.pitch - F.guard; p += 64)
@@ -270,7 +278,8 @@ __global__ __launch_bounds__(64 * H * (K + 1)) __attribute__((amdgpu_waves_per_e
     const int pairs = (S.strips + H - 1) / H;
     const int strip = (int)(wg % (unsigned)pairs) * H + h;   // may be one past the last: an idle half
     const int a = (int)(wg / (unsigned)pairs) * S.seg_rows, b = min(a + S.seg_rows, F.nr + 1);
-    const int j = strip * (64 - 2 * K) + lane, jc = min(j, F.nth);
+    const FieldStrips cut(K, F.nth);
+    const int j = cut.first_column(strip) + lane, jc = min(j, F.nth);
     const bool axis = j == 0 || j >= F.nth;
     const int m0 = max(a - K, 0);                       // the first row read
     const int steps = b - m0 + 2 * K;                   // row b comes to the last pass in the last one
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(64 * H * (K + 1)) __attribute__((amdgpu_waves_per_e
         return;
     }
 
-    const bool owned = j <= F.nth && (strip == 0 || lane >= K) && (strip == S.strips - 1 || lane < 64 - K);
+    const bool owned = cut.stores(strip, lane), mirrors = cut.mirrors(strip, F.guard);
     const bool beyond = j >= F.nth;
     ColK ci, ch;                                        // columns j and j + 1/2
     {
@@ -406,7 +415,7 @@ __global__ __launch_bounds__(64 * H * (K + 1)) __attribute__((amdgpu_waves_per_e
                         if (owned)
                             for (int c = 0; c < 6; ++c) *elem(out.c[c], e) = v[c];
                     } else {
-                        store_state(F, out, S, r, j, lane, owned, strip == 0, strip == S.strips - 1, v);
+                        store_state(F, out, S, r, j, lane, owned, mirrors, strip == cut.count - 1, v);
                     }
                 }
             }
@@ -451,8 +460,7 @@ constexpr int kCus = 256, kMinSegRows = 6;
 template <int K, bool FIRST>
 static void launch_march(const FieldArgs& F, FieldPtrs in, FieldPtrs R, FieldPtrs out, StageArgs S,
                          hipStream_t stream) {
-    const int valid = 64 - 2 * K;
-    S.strips = 1 + (std::max(F.nth + 1 - 64, 0) + valid - 1) / valid;
+    S.strips = FieldStrips(K, F.nth).count;
     const int most = (F.nr + kMinSegRows) / kMinSegRows;
     const bool two = (int64_t)S.strips * most > kCus;
     const int units = two ? (S.strips + 1) / 2 : S.strips;

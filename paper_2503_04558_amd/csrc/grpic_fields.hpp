@@ -49,6 +49,28 @@ inline size_t field_workspace_bytes(int nr, int pitch, int guard) {
     return sizeof(double) * 18 * field_plane(nr, pitch, guard);
 }
 
+// Strips of 64 columns that a launch of K passes cuts columns 0 .. nth into:
+// strip s loads columns s (64 - 2 K) and the 63 after it and stores those of
+// them whose K neighbours on either side it holds too (the axes have none).
+struct FieldStrips {
+    int K, nth, count;
+    __host__ __device__ FieldStrips(int K_, int nth_) : K(K_), nth(nth_), count(1) {
+        const int rest = nth + 1 - 64;
+        if (rest > 0) count += (rest + 63 - 2 * K) / (64 - 2 * K);
+    }
+    __host__ __device__ int first_column(int s) const { return s * (64 - 2 * K); }
+    __host__ __device__ bool stores(int s, int lane) const {
+        return first_column(s) + lane <= nth && (s == 0 || lane >= K) && (s == count - 1 || lane < 64 - K);
+    }
+    // Does strip s store columns within `guard` of an axis, whose values the
+    // columns beyond it take too?  They need not lie in the first or the last
+    // strip: the last one stores as few as K + 1 columns.
+    __host__ __device__ bool mirrors(int s, int guard) const {
+        return first_column(s) + (s == 0 ? 0 : K) <= guard ||
+               (s == count - 1 ? nth : first_column(s) + 63 - K) >= nth - guard;
+    }
+};
+
 hipError_t launch_field_tables(const FieldArgs& F, const double* gx, const double* gw, hipStream_t stream);
 hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, FieldPtrs W1, FieldPtrs W2, int ncorr,
                              int damp_cells, double damp_max, hipStream_t stream);
