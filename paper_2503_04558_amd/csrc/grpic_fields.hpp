@@ -52,6 +52,7 @@ inline size_t field_workspace_bytes(int nr, int pitch, int guard) {
 // Strips of 64 columns that a launch of K passes cuts columns 0 .. nth into:
 // strip s loads columns s (64 - 2 K) and the 63 after it and stores those of
 // them whose K neighbours on either side it holds too (the axes have none).
+// A workgroup of two strips may hold one past the last: it stores nothing.
 struct FieldStrips {
     int K, nth, count;
     __host__ __device__ FieldStrips(int K_, int nth_) : K(K_), nth(nth_), count(1) {
@@ -60,7 +61,8 @@ struct FieldStrips {
     }
     __host__ __device__ int first_column(int s) const { return s * (64 - 2 * K); }
     __host__ __device__ bool stores(int s, int lane) const {
-        return first_column(s) + lane <= nth && (s == 0 || lane >= K) && (s == count - 1 || lane < 64 - K);
+        return s < count && first_column(s) + lane <= nth && (s == 0 || lane >= K) &&
+               (s == count - 1 || lane < 64 - K);
     }
     // Does strip s store columns within `guard` of an axis, whose values the
     // columns beyond it take too?  They need not lie in the first or the last
