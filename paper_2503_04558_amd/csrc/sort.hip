@@ -70,8 +70,6 @@ __global__ __launch_bounds__(256) void sort_setup(const SortArgs S, int64_t len,
 constexpr int kChunkThreads = 256;
 constexpr int kChunkItems = 8;
 constexpr int kChunk = kChunkThreads * kChunkItems;
-constexpr int kHashBits = 12;
-constexpr int kHashSlots = 1 << kHashBits;
 static_assert(kHashSlots == 2 * kChunk, "at most half full");
 constexpr int kEmpty = -1;
 
@@ -87,32 +85,21 @@ __device__ __forceinline__ void table_clear(CellSlot* T) {
     for (int e = threadIdx.x; e < kHashSlots; e += kChunkThreads) T[e].base = 0x00000000FFFFFFFFull;   // kEmpty, 0
 }
 
-// Slot of place t in probing order: blocks of 16 slots, all blocks' first
-// slots, then all their second ones, ...
-__device__ __forceinline__ int slot_of(int t) {
-    constexpr int kBlocks = kHashSlots / 16;
-    return (t & (kBlocks - 1)) << 4 | t / kBlocks;
-}
-
 // Slot of cell c (inserted if new); adds inc to its count and returns the
-// count before the add in old.  Blocks of 16 cells, whose counters share a
-// 128-byte line, are hashed (multiplicatively: cells c and c + nth of
-// neighbouring rows must not collide) and keep their cells' order inside the
-// block, so that consecutive threads of the flush add to consecutive
-// counters: an atomic per line instead of one per cell (histogram of 2e7
-// drifted particles on 2048 x 2048 0.58 -> 0.20 ms, re-sort of 2e8 0.80 ->
-// 0.54 ms).  Probing goes to the same place of the next block, and after the
-// last block to the next place, so it reaches every slot.
+// count before the add in old.  The cells of a 128-byte line of counters lie
+// in neighbouring slots (CellPlace), so that consecutive threads of the flush
+// add to consecutive counters: an atomic per line instead of one per cell
+// (histogram of 2e7 drifted particles on 2048 x 2048 0.58 -> 0.20 ms, re-sort
+// of 2e8 0.80 -> 0.54 ms).
 __device__ __forceinline__ int table_insert(CellSlot* T, int c, int inc, int& old) {
-    int t = (c & 15) << (kHashBits - 4) | (int)(((unsigned)(c >> 4) * 2654435761u) >> (36 - kHashBits));
-    for (int probe = 0; probe < kHashSlots; ++probe) {
-        const int slot = slot_of(t);
+    CellPlace at(c);
+    for (int probe = 0; probe < kHashSlots; ++probe, at.next()) {
+        const int slot = at.slot();
         const int k = atomicCAS(&T[slot].key, kEmpty, c);
         if (k == kEmpty || k == c) {
             old = atomicAdd(&T[slot].count, inc);
             return slot;
         }
-        t = (t + 1) & (kHashSlots - 1);
     }
     old = 0;                           // not reached: at most kChunk keys in 2 * kChunk slots
     return -1;
