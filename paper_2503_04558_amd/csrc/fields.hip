@@ -448,28 +448,16 @@ hipError_t launch_field_tables(const FieldArgs& F, const double* gx, const doubl
     return hipGetLastError();
 }
 
-// Workgroups of one launch.  A workgroup's LDS (73.7 to 76.8 KB per strip with
-// four passes) and its odd number of waves let a CU hold one workgroup of two
-// strips, or one of one strip (two five-wave workgroups do not share a CU:
-// their first SIMDs collide, measured 695 against 475 us per 2048 x 2048
-// step).  So: one strip per workgroup while segments of kMinSegRows rows fit
-// one round of 256 workgroups (a step of 256 x 256: 38 us against 46), else
-// two strips and segments cut for one round.
-constexpr int kCus = 256, kMinSegRows = 6;
-
 template <int K, bool FIRST>
 static void launch_march(const FieldArgs& F, FieldPtrs in, FieldPtrs R, FieldPtrs out, StageArgs S,
                          hipStream_t stream) {
-    S.strips = FieldStrips(K, F.nth).count;
-    const int most = (F.nr + kMinSegRows) / kMinSegRows;
-    const bool two = (int64_t)S.strips * most > kCus;
-    const int units = two ? (S.strips + 1) / 2 : S.strips;
-    const int segs = std::max(1, std::min(kCus / units, most));
-    S.seg_rows = (F.nr + segs) / segs;                  // ceil((nr + 1) / segs)
-    S.nwg = (unsigned)(units * ((F.nr + S.seg_rows) / S.seg_rows));
+    const FieldMarch L(K, F.nr, F.nth, F.plane);
+    S.strips = L.strips;
+    S.seg_rows = L.seg_rows;
+    S.nwg = (unsigned)L.workgroups;
     S.per_xcd = (S.nwg + 7) / 8;
     const dim3 grid(8 * S.per_xcd);
-    if (two)
+    if (L.two)
         hipLaunchKernelGGL((field_march_kernel<K, FIRST, 2>), grid, dim3(128 * (K + 1)), 0, stream, F, in, R, out, S,
                            F.tab, F.rad, F.drow);
     else

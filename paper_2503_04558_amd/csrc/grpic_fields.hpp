@@ -73,6 +73,40 @@ struct FieldStrips {
     }
 };
 
+// Workgroups of one launch of K passes: strips and segments of rows.
+// A workgroup's LDS (73.7 to 76.8 KB per strip with four passes) and its odd
+// number of waves let a CU hold one workgroup of two strips, or one of one
+// strip (two five-wave workgroups do not share a CU: their first SIMDs collide,
+// measured 695 against 475 us per 2048 x 2048 step).  So with four passes: one
+// strip per workgroup while segments of kMinSegRows rows fit one round of 256
+// workgroups (a step of 256 x 256: 38 us against 46), else two strips and
+// segments cut for one round.
+// With fewer passes two one-strip workgroups can share a CU, which halves the
+// segments.  That pays where the march's steps are the bound and not HBM: where
+// a launch's arrays (24 planes) fit the 256 MB Infinity Cache, and on grids of one
+// or three strips, where workgroups of two would leave a half idle.  Four
+// passes in two launches: 20000 x 16 (one strip) 195 us in workgroups of two
+// strips, 108 so, 20000 x 130 (three) 406 and 302, 2000 x 500 (194 MB) 111 and 97;
+// but two strips in step read their halo columns once: 20000 x 400 (1.55 GB,
+// seven) 792 and 813, 2048 x 2048 (0.81 GB) 400 and 422.
+struct FieldMarch {
+    static constexpr int kCus = 256, kMinSegRows = 6, kNarrow = 3, kMaxPasses = 4;
+    static constexpr size_t kCacheBytes = (size_t)256 << 20;
+    int strips, seg_rows, workgroups;
+    bool two;                                     // two strips per workgroup
+    FieldMarch(int K, int nr, int nth, size_t plane) : strips(FieldStrips(K, nth).count) {
+        const int most = (nr + kMinSegRows) / kMinSegRows;
+        const bool narrow = strips <= kNarrow && strips % 2 == 1;
+        const bool share = K < kMaxPasses && (narrow || 24 * sizeof(double) * plane <= kCacheBytes);
+        two = !share && (int64_t)strips * most > kCus;
+        const int units = two ? (strips + 1) / 2 : strips;
+        int segs = (share ? 2 * kCus : kCus) / units;
+        segs = segs < 1 ? 1 : segs > most ? most : segs;
+        seg_rows = (nr + segs) / segs;            // ceil((nr + 1) / segs)
+        workgroups = units * ((nr + seg_rows) / seg_rows);
+    }
+};
+
 hipError_t launch_field_tables(const FieldArgs& F, const double* gx, const double* gw, hipStream_t stream);
 hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, FieldPtrs W1, FieldPtrs W2, int ncorr,
                              int damp_cells, double damp_max, hipStream_t stream);

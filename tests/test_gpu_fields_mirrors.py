@@ -35,6 +35,7 @@ def _state(g, seed):
     (8, 122, 4, 0, 5),                                                            # of three
     (8, 120, 5, 3, 7),                                                            # of four
     (6, 300, 65, 0, 7), (6, 300, 70, 1, 1),                                       # wider than a strip
+    (4000, 9, 2, 0, 0), (3500, 16, 2, 1, 1), (1700, 130, 2, 0, 2), (3100, 30, 3, 0, 4),   # tall: short segments
 ])
 def test_mirrors_match_oracle(nr, nth, guard, pad, ncorr):
     print(f"[gpu] field mirrors {nr}x{nth} guard={guard} pad={pad} ncorr={ncorr}", flush=True)
