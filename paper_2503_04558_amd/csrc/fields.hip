@@ -474,22 +474,23 @@ static void launch_passes(int K, const FieldArgs& F, FieldPtrs in, FieldPtrs R, 
     else launch_march<4, FIRST>(F, in, R, out, S, stream);
 }
 
-// The step's 1 + ncorr passes in launches of up to kMaxStages, at least two:
-// the first reads X and leaves R, the last writes X, those between alternate
-// between W1 and W2.  A step of one pass (no corrector) reads a copy of X.
+// The step's 1 + ncorr passes in launches of up to kMaxStages.  Steps of one or
+// two passes run in one launch that reads a copy of X (33 planes of traffic
+// with the copy, 51 in two launches); others in at least two: the first reads X
+// and leaves R, the last writes X, those between alternate between W1 and W2.
 hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, FieldPtrs W1, FieldPtrs W2, int ncorr,
                              int damp_cells, double damp_max, hipStream_t stream) {
     StageArgs S{};
     S.damp_cells = damp_cells;
     S.damp_max = damp_max;
-    if (ncorr == 0) {
+    const int passes = ncorr + 1;
+    if (passes <= 2) {
         const int64_t n_all = (int64_t)(F.nr + 1 + 2 * F.guard) * F.pitch;
         hipLaunchKernelGGL(field_copy_kernel, dim3(nb(n_all)), dim3(256), 0, stream, W2, X, n_all);
         S.last = 1;
-        launch_march<1, true>(F, W2, R, X, S, stream);
+        launch_passes<true>(passes, F, W2, R, X, S, stream);
         return hipGetLastError();
     }
-    const int passes = ncorr + 1;
     const int launches = std::max(2, (passes + kMaxStages - 1) / kMaxStages);
     FieldPtrs cur = X;
     for (int g = 0; g < launches; ++g) {

@@ -110,3 +110,19 @@ def test_cubic_push_after_a_step_reads_fresh_columns():
     for k in ("xr", "xth", "ur", "uth", "uph"):
         err = np.abs(out[k][live] - ref[k][live]) / (1.0 + np.abs(ref[k][live]))
         assert err.max() <= 1e-11, (k, err.max())
+
+
+@pytest.mark.parametrize("ncorr,launches", [(0, 1), (1, 1), (2, 2)])
+def test_short_steps_take_one_launch(ncorr, launches):
+    """A step of one or two passes reads a copy of the state (the third six
+    planes of the workspace) and needs neither the corrector's constant part
+    nor an iterate in memory: the first twelve planes keep what they held.
+    (Two launches of a pass each move half as much again; on 100000 x 250 they
+    were slower than a pass at a time through tiles had been.)"""
+    g = wl.make_grid(40, 100, 0.9)
+    solver = grpic.FieldSolver(grpic.make_metric(g.a, g.M), g)
+    ws = solver.ws.view(torch.float64).view((18,) + g.shape)
+    ws.fill_(7.0)
+    st = list(torch.randn((6,) + g.shape, dtype=torch.float64, device="cuda"))
+    solver.step(st, None, wl.crossing_dt(g), 0.53, ncorr)
+    assert bool((ws[:12] == 7.0).all()) == (launches == 1)
