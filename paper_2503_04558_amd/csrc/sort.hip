@@ -2,7 +2,7 @@
 // push kernel runs on.
 //
 // histogram of live cells -> exclusive scan (4096 entries per block, two
-// launches) -> [tiling: per-tile slice counts of both cuts -> scan -> slice
+// launches, three on the largest grids) -> [tiling: per-tile slice counts of both cuts -> scan -> slice
 // tables] ->
 // scatter.  Histogram and scatter take a chunk of consecutive particles per
 // workgroup and count its cells in an LDS hash table first, so each distinct
@@ -21,6 +21,12 @@ namespace grpic {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
+// Up to this many tiles every block of the scan's second launch sums the totals
+// before it (a launch fewer: sort of 1e3 particles on 4096 x 4096, 4097 tiles, 251
+// us against 261); the sums grow with the square of the tiles, so beyond it the
+// totals are scanned by a block of their own (8192 x 4096, 8193 tiles, 475 against
+// 466; 23000 x 23000, 129,151 tiles, 11.2 against 7.1 ms).
+constexpr unsigned kScanSelfSum = 8192;
 
 int64_t sort_scan_blocks(int64_t len) { return (len + kScanTile - 1) / kScanTile; }
 
@@ -220,19 +226,47 @@ __global__ __launch_bounds__(256) void scan_tiles(V values, unsigned long long* 
     if (threadIdx.x == kScanThreads - 1) blocksums[blockIdx.x] = incl;
 }
 
-// Adds the totals of the tiles before it to each tile (every block sums them
-// itself: a launch fewer than a scan of the totals); copies of the result
-// go to offsets and its last entry to last, where given.
+// Exclusive scan of the tile totals in place, by one block.
+__global__ __launch_bounds__(256) void scan_totals(unsigned long long* __restrict__ blocksums, int64_t nb) {
+    __shared__ unsigned long long sh[kScanThreads];
+    unsigned long long carry = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += kScanTile) {
+        const int64_t base = c0 + (int64_t)threadIdx.x * kScanItems;
+        unsigned long long v[kScanItems];
+        unsigned long long tot = 0;
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = base + k < nb ? blocksums[base + k] : 0ull;
+            tot += v[k];
+        }
+        const unsigned long long incl = block_inclusive_scan(tot, sh);
+        unsigned long long run = carry + incl - tot;
+        for (int k = 0; k < kScanItems; ++k) {
+            if (base + k < nb) blocksums[base + k] = run;
+            run += v[k];
+        }
+        carry += sh[kScanThreads - 1];
+        __syncthreads();                                 // sh is written again
+    }
+}
+
+// Adds the totals of the tiles before it to each tile: their sum, which every
+// block forms itself, or the scanned totals' entry (SCANNED); copies of the
+// result go to offsets and its last entry to last, where given.
+template <bool SCANNED>
 __global__ __launch_bounds__(256) void scan_finish(unsigned long long* __restrict__ a, int64_t len,
                                                    const unsigned long long* __restrict__ blocksums,
                                                    int64_t* __restrict__ offsets, int64_t* __restrict__ last) {
     __shared__ unsigned long long part[4];
     unsigned long long v = 0;
-    for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) v += blocksums[i];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    v = part[0] + part[1] + part[2] + part[3];
+    if constexpr (SCANNED) {
+        v = blocksums[blockIdx.x];
+    } else {
+        for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) v += blocksums[i];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+        __syncthreads();
+        v = part[0] + part[1] + part[2] + part[3];
+    }
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = (int64_t)blockIdx.x * kScanTile + k * 256 + threadIdx.x;
         if (i >= len) return;
@@ -252,7 +286,12 @@ static void scan_into(V v, unsigned long long* a, int64_t len, unsigned long lon
                       int64_t* last, hipStream_t stream) {
     const dim3 nb((unsigned)sort_scan_blocks(len));
     hipLaunchKernelGGL(scan_tiles<V>, nb, dim3(kScanThreads), 0, stream, v, a, len, blocksums);
-    hipLaunchKernelGGL(scan_finish, nb, dim3(256), 0, stream, a, len, blocksums, offsets, last);
+    if (nb.x > kScanSelfSum) {
+        hipLaunchKernelGGL(scan_totals, dim3(1), dim3(kScanThreads), 0, stream, blocksums, (int64_t)nb.x);
+        hipLaunchKernelGGL(scan_finish<true>, nb, dim3(256), 0, stream, a, len, blocksums, offsets, last);
+    } else {
+        hipLaunchKernelGGL(scan_finish<false>, nb, dim3(256), 0, stream, a, len, blocksums, offsets, last);
+    }
 }
 
 void scan_exclusive(unsigned long long* a, int64_t len, unsigned long long* blocksums, hipStream_t stream) {
