@@ -252,20 +252,24 @@ def run_adjoint(args):
             "dense_lambda_bwd_ms": min(bd), "dense_lambda_bwd_over_fwd": min(bd) / min(f_ck)}
 
 
-# Field step: grid planes that it must move at least, with the metric
-# coefficients formed in registers, the six inverse areas tabulated and the
-# corrector's constant part R = X^n + dt (w0 C(X^n) - J) formed once.  A launch
+# Field step: grid planes that its launches must move at least, with the metric
+# coefficients formed in registers and the six inverse areas tabulated.  A launch
 # carries up to four passes (predictor and correctors) over one read of its
-# inputs, a step has at least two launches: the first reads the state, inverse
-# areas and currents (3) and writes the iterate and R, a later one reads the
-# iterate, R and the inverse areas and writes the iterate.  CORRECTOR is the
-# later launches' share of one of the default step's 7 correctors.
+# inputs.  A step of one or two passes is one launch: it reads the state (a copy
+# of it, which is not counted), inverse areas and currents (3) and writes the
+# state.  A longer one takes at least two: the first writes the iterate and the
+# corrector's constant part R = X^n + dt (w0 C(X^n) - J) instead, a later one
+# reads the iterate, R and the inverse areas and writes the iterate.  CORRECTOR
+# is 1/7 of the one later launch that the default step's 7 correctors take.
+FIELD_PLANES_SHORT_STEP = 6 + 6 + 3 + 6
 FIELD_PLANES_PREDICTOR = 6 + 6 + 3 + 6 + 6
 FIELD_PLANES_LATER_LAUNCH = 6 + 6 + 6 + 6
 FIELD_PLANES_CORRECTOR = FIELD_PLANES_LATER_LAUNCH / 7
 
 
 def field_planes(ncorr: int) -> int:
+    if ncorr <= 1:
+        return FIELD_PLANES_SHORT_STEP
     launches = max(2, (ncorr + 1 + 3) // 4)
     return FIELD_PLANES_PREDICTOR + (launches - 1) * FIELD_PLANES_LATER_LAUNCH
 
