@@ -252,9 +252,16 @@ def make_current(g, J) -> grpic_current:
     return grpic_current(*[t.data_ptr() for t in J])
 
 
+# The current stream's handle without a Stream object around it, where this
+# torch has it (an internal function of torch).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
-    if stream is None:                                  # the handle itself, without a Stream object around it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     return getattr(stream, "cuda_stream", stream)
 
 
