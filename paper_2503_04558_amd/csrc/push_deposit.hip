@@ -485,8 +485,8 @@ template <int SERIES, int KICK, int ORDER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64(const StepArgs A) {
     push_deposit_body<false, SERIES, KICK, ORDER>(A);
 }
-// The cubic shape's kernel (96 gather loads, a 5 x 5 deposit), at three
-// waves per SIMD like the CIC kernel (its gather loads one component at a
+// The cubic shape's kernel (96 gathered values in 48 loads, a 5 x 5 deposit), at
+// three waves per SIMD like the CIC kernel (its gather loads one component at a
 // time).
 template <int SERIES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void push_deposit_f64_spline3(const StepArgs A) {
@@ -743,11 +743,12 @@ __global__ __launch_bounds__(256) void slice_live_sum(const int32_t* __restrict_
 
 // THREADS: the tiling's slice size (kSliceThreads).  The CIC kernels run at
 // four waves per SIMD (114 VGPRs; four workgroups' LDS fit a CU).  What bounds
-// them is FP64 issue: 2e8 particles on 2048 x 2048 in 7.9 ms a step where the
-// right-hand side of 98 operations a point and two Newton steps per estimate
-// took 9.0; with the long series and the library's sin and cos at the poles
-// (131 VGPRs, three waves) 2e5 particles on 256 x 256 took 21 us a step, now
-// 17.
+// them is FP64 issue: 2e8 particles on 2048 x 2048 in 8.57 ms a step (the mean
+// of the 20 between two re-sorts; 8.2 right after one) where the right-hand side
+// of 98 operations a point and two Newton steps per estimate took 9.26 (9.0).
+// With the long series and the library's sin and cos at the poles (131 VGPRs,
+// three waves) 2e5 particles on 256 x 256 took 21 us a step, now 17.  A fifth wave
+// needs 96 VGPRs and no staged states: 18 of them spill (68 bytes a lane), 11.8 ms.
 template <int THREADS, int SERIES, int KICK>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(SERIES == kPlain ? 3 : 4))) void push_deposit_f64_tiled(
     const StepArgs A, const Slice* __restrict__ slices, int64_t slice_cap,
@@ -984,7 +985,10 @@ static void with_series(const StepArgs& A, F&& f) {
 
 // Particles in any order.  Sets that leave CUs without a 256-lane workgroup
 // run one-wave ones, so that they spread over all CUs (the step is one long
-// dependent chain per wave: 2e4 particles 16.0 -> 14.2 us).
+// dependent chain per wave).  Passes of two steps and the resets, 256 lanes
+// against 64: FP64 2e4 particles on 256 x 256 35.1 and 33.1 us, 65,536 72.9 and 72.2,
+// 1e5 on 1024 x 1024 121 and 128; cubic 300 79 and 35, 5e3 82 and 51, 65,536 414 and
+// 414, 1e5 616 and 631; split 2e4 38.5 and 36.7, 1e5 101 and 101.
 hipError_t launch_push_deposit(const StepArgs& A, bool split, hipStream_t stream, int kick, int order) {
     if (A.n <= 0) return hipSuccess;
     const unsigned threads = A.n <= 256 * 256 ? 64 : 256;
