@@ -137,6 +137,7 @@ struct StageArgs {
     unsigned nwg, per_xcd;                              // strips x segments, and an XCD's share of them
     int last;                                           // the step's last launch: out is the state
     int store_R;                                        // a later launch needs R
+    int pad_end;                                        // the guard rows' padding that the last launch writes
     int damp_cells;
     double damp_max;
 };
@@ -244,7 +245,7 @@ __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs&
         }
         // the guard rows' columns beyond the mirrored ones repeat the edge row's
         if (last_strip && lo < hi)
-            for (int p = F.nth + F.guard + (chalf ? 0 : 1) + lane; p < F.pitch - F.guard; p += 64)
+            for (int p = F.nth + F.guard + (chalf ? 0 : 1) + lane; p < S.pad_end; p += 64)
                 for (int q = lo; q <= hi; ++q)
                     if (q != r) *elem(out.c[c], F.at(q, p)) = *elem(out.c[c], F.at(r, p));
     }
@@ -426,10 +427,28 @@ __global__ __launch_bounds__(64 * H * (K + 1)) __attribute__((amdgpu_waves_per_e
     }
 }
 
-__global__ __launch_bounds__(256) void field_copy_kernel(FieldPtrs dst, FieldPtrs src, int64_t n) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    for (int c = 0; c < 6; ++c) dst.c[c][t] = src.c[c][t];
+// `runs` runs of `width` elements of the six arrays, a row apart, from e0.
+__global__ __launch_bounds__(256) void field_copy_kernel(FieldArgs F, FieldPtrs dst, FieldPtrs src, uint32_t e0,
+                                                         uint32_t runs, uint32_t width) {
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x, i = runs == 1u ? 0u : t / width;
+    if (i >= runs || t - i * width >= width) return;
+    const uint32_t e = e0 + i * (uint32_t)F.pitch + (t - i * width);
+    for (int c = 0; c < 6; ++c) *elem(dst.c[c], e) = *elem(src.c[c], e);
+}
+
+// The guard rows' columns beyond the mirrored ones repeat the edge row's, which
+// a step leaves alone (as store_state does where they are few).
+__global__ __launch_bounds__(256) void field_pad_kernel(FieldArgs F, FieldPtrs X, uint32_t width) {
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x, k = t / width;
+    const int p = F.nth + F.guard + (int)(t - k * width);
+    if (k > 2u * (uint32_t)F.guard) return;
+    const int q = (int)k < F.guard ? (int)k - F.guard : F.nr + (int)k - F.guard;   // -guard .. -1, nr .. nr + guard
+    for (int c = 0; c < 6; ++c) {
+        const bool half = c == 0 || c > 3, chalf = c == 1 || c == 3 || c == 5;
+        const int edge = q < 0 ? 0 : half ? F.nr - 1 : F.nr;
+        if (q == edge || (!chalf && p == F.nth + F.guard)) continue;
+        *elem(X.c[c], F.at(q, p)) = *elem(X.c[c], F.at(edge, p));
+    }
 }
 
 inline unsigned nb(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -484,9 +503,23 @@ hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, Field
     S.damp_cells = damp_cells;
     S.damp_max = damp_max;
     const int passes = ncorr + 1;
+    // The guard rows' padding, pads columns of it: by the last launch's last strip
+    // while a wave's store does, else by a launch of its own (1000 x 1000 with 3000
+    // columns of padding, a step with a corrector: 292 us in the strip, which walks
+    // them 64 at a time, 76 so).
+    const int pads = F.pitch - 2 * F.guard - F.nth;      // from column nth + guard
+    S.pad_end = pads <= 64 ? F.pitch - F.guard : 0;
+    if (pads > 64)
+        hipLaunchKernelGGL(field_pad_kernel, dim3(nb((int64_t)(2 * F.guard + 1) * pads)), dim3(256), 0, stream, F, X,
+                           (uint32_t)pads);
     if (passes <= 2) {
-        const int64_t n_all = (int64_t)(F.nr + 1 + 2 * F.guard) * F.pitch;
-        hipLaunchKernelGGL(field_copy_kernel, dim3(nb(n_all)), dim3(256), 0, stream, W2, X, n_all);
+        // rows 0 .. nr, columns 0 .. nth are read: copied in one run while the padding is a sixteenth at most
+        // (2048 x 2048: 265 us a step, 268 row by row; with 2048 columns of padding 486, 272 row by row)
+        const bool one = F.pitch <= F.nth + 1 + 2 * F.guard + F.nth / 16;
+        const uint32_t runs = one ? 1u : (uint32_t)F.nr + 1u;
+        const uint32_t width = one ? F.at(F.nr, F.nth) - F.at(0, 0) + 1u : (uint32_t)F.nth + 1u;
+        hipLaunchKernelGGL(field_copy_kernel, dim3(nb((int64_t)runs * width)), dim3(256), 0, stream, F, W2, X, F.at(0, 0),
+                           runs, width);
         S.last = 1;
         launch_passes<true>(passes, F, W2, R, X, S, stream);
         return hipGetLastError();
