@@ -137,7 +137,7 @@ struct StageArgs {
     unsigned nwg, per_xcd;                              // strips x segments, and an XCD's share of them
     int last;                                           // the step's last launch: out is the state
     int store_R;                                        // a later launch needs R
-    int pad_end;                                        // the guard rows' padding that the last launch writes
+    int guard_rows, pad_end;                            // guard rows that the last launch writes, end of their columns
     int damp_cells;
     double damp_max;
 };
@@ -234,11 +234,12 @@ __device__ __forceinline__ void store_state(const FieldArgs& F, const FieldPtrs&
             for (int c = 0; c < 6; ++c) mirror(c, r);
         return;
     }
+    // (with no guard rows of its own this also stores row nr of the half-row components, one of them)
     for (int c = 0; c < 6; ++c) {
         const bool half = c == 0 || c > 3, chalf = c == 1 || c == 3 || c == 5;
         const int top = half ? F.nr - 1 : F.nr;
         if (r > top) continue;
-        const int lo = r == 0 ? -F.guard : r, hi = r == top ? F.nr + F.guard : r;
+        const int lo = r == 0 ? -S.guard_rows : r, hi = r == top ? F.nr + S.guard_rows : r;
         for (int q = lo; q <= hi; ++q) {
             put(c, q);
             if (mirrors) mirror(c, q);
@@ -436,18 +437,15 @@ __global__ __launch_bounds__(256) void field_copy_kernel(FieldArgs F, FieldPtrs 
     for (int c = 0; c < 6; ++c) *elem(dst.c[c], e) = *elem(src.c[c], e);
 }
 
-// The guard rows' columns beyond the mirrored ones repeat the edge row's, which
-// a step leaves alone (as store_state does where they are few).
-__global__ __launch_bounds__(256) void field_pad_kernel(FieldArgs F, FieldPtrs X, uint32_t width) {
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x, k = t / width;
-    const int p = F.nth + F.guard + (int)(t - k * width);
+// The guard rows, all columns, from the edge rows (zero gradient).
+__global__ __launch_bounds__(256) void field_guard_rows_kernel(FieldArgs F, FieldPtrs X) {
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x, k = t / (uint32_t)F.pitch;
+    const int j = (int)(t - k * (uint32_t)F.pitch) - F.guard;
     if (k > 2u * (uint32_t)F.guard) return;
     const int q = (int)k < F.guard ? (int)k - F.guard : F.nr + (int)k - F.guard;   // -guard .. -1, nr .. nr + guard
     for (int c = 0; c < 6; ++c) {
-        const bool half = c == 0 || c > 3, chalf = c == 1 || c == 3 || c == 5;
-        const int edge = q < 0 ? 0 : half ? F.nr - 1 : F.nr;
-        if (q == edge || (!chalf && p == F.nth + F.guard)) continue;
-        *elem(X.c[c], F.at(q, p)) = *elem(X.c[c], F.at(edge, p));
+        const int edge = q < 0 ? 0 : c == 0 || c > 3 ? F.nr - 1 : F.nr;
+        if (q != edge) *elem(X.c[c], F.at(q, j)) = *elem(X.c[c], F.at(edge, j));
     }
 }
 
@@ -493,6 +491,8 @@ static void launch_passes(int K, const FieldArgs& F, FieldPtrs in, FieldPtrs R, 
     else launch_march<4, FIRST>(F, in, R, out, S, stream);
 }
 
+constexpr int kFewGuardRows = 6;
+
 // The step's 1 + ncorr passes in launches of up to kMaxStages.  Steps of one or
 // two passes run in one launch that reads a copy of X (33 planes of traffic
 // with the copy, 51 in two launches); others in at least two: the first reads X
@@ -503,15 +503,20 @@ hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, Field
     S.damp_cells = damp_cells;
     S.damp_max = damp_max;
     const int passes = ncorr + 1;
-    // The guard rows' padding, pads columns of it: by the last launch's last strip
-    // while a wave's store does, else by a launch of its own (1000 x 1000 with 3000
-    // columns of padding, a step with a corrector: 292 us in the strip, which walks
-    // them 64 at a time, 76 so).
-    const int pads = F.pitch - 2 * F.guard - F.nth;      // from column nth + guard
-    S.pad_end = pads <= 64 ? F.pitch - F.guard : 0;
-    if (pads > 64)
-        hipLaunchKernelGGL(field_pad_kernel, dim3(nb((int64_t)(2 * F.guard + 1) * pads)), dim3(256), 0, stream, F, X,
-                           (uint32_t)pads);
+    // Guard rows: by the last launch's waves at the edge rows while they and their
+    // padding are few, else by a launch of their own, as those waves store them one
+    // after another.  256 x 256, no corrector: 6 guard rows 20.3 us in the waves and
+    // 19.8 apart, 8 22 and 20, 100 90 and 21 (1000 x 1000: 6 61 and 63, 8 62 and 61);
+    // 1000 x 1000 with 3000 columns of padding, one corrector, 292 and 76 us.
+    const bool apart = F.guard > kFewGuardRows || F.pitch - F.nth - 2 * F.guard > 64;
+    S.guard_rows = apart ? 0 : F.guard;
+    S.pad_end = apart ? 0 : F.pitch - F.guard;
+    auto finish = [&] {
+        if (apart)
+            hipLaunchKernelGGL(field_guard_rows_kernel, dim3(nb((int64_t)(2 * F.guard + 1) * F.pitch)), dim3(256), 0,
+                               stream, F, X);
+        return hipGetLastError();
+    };
     if (passes <= 2) {
         // rows 0 .. nr, columns 0 .. nth are read: copied in one run while the padding is a sixteenth at most
         // (2048 x 2048: 265 us a step, 268 row by row; with 2048 columns of padding 486, 272 row by row)
@@ -522,7 +527,7 @@ hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, Field
                            runs, width);
         S.last = 1;
         launch_passes<true>(passes, F, W2, R, X, S, stream);
-        return hipGetLastError();
+        return finish();
     }
     const int launches = std::max(2, (passes + kMaxStages - 1) / kMaxStages);
     FieldPtrs cur = X;
@@ -535,7 +540,7 @@ hipError_t launch_field_step(const FieldArgs& F, FieldPtrs X, FieldPtrs R, Field
         else launch_passes<false>(K, F, cur, R, nxt, S, stream);
         cur = nxt;
     }
-    return hipGetLastError();
+    return finish();
 }
 
 }  // namespace grpic

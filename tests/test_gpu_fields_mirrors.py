@@ -37,6 +37,7 @@ def _state(g, seed):
     (6, 300, 65, 0, 7), (6, 300, 70, 1, 1),                                       # wider than a strip
     (4000, 9, 2, 0, 0), (3500, 16, 2, 1, 1), (1700, 130, 2, 0, 2), (3100, 30, 3, 0, 4),   # tall: short segments
     (12, 200, 2, 63, 1), (12, 200, 2, 64, 1), (9, 60, 3, 200, 0), (2, 8, 2, 130, 7), (14, 130, 4, 90, 3),   # wide padding
+    (15, 40, 6, 0, 2), (15, 40, 7, 3, 2), (20, 64, 12, 0, 7), (2, 200, 100, 1, 0),   # guard rows in the waves, apart
     (40, 300, 2, 18, 1), (40, 300, 2, 19, 0),                                     # copied in one run, row by row
 ])
 def test_mirrors_match_oracle(nr, nth, guard, pad, ncorr):
